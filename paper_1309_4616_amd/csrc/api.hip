@@ -38,7 +38,7 @@ namespace expi {
 bool pair2d_supported(const Op& op, int tw);
 bool pair2d_rows_valid(int rows);
 hipError_t launch_pair2d(const Op& op, int tw, PairArgs a, hipStream_t s, hipEvent_t after_sweep, bool finalize,
-                         int mode, int cus, int rows);
+                         int mode, int cus, int rows, int* nparts = nullptr);
 int device_cus();
 
 namespace {
@@ -52,12 +52,12 @@ bool pairs_on(const Op& op, int tw) { return op.use_pairs != 0 && pair_any_suppo
 // The pair sweep of the operator's dimension.  A 2D operator's use_pairs
 // above 1 is the rows per tile of its pair sweep (expi_op_set_pairs).
 hipError_t launch_pair_op(const Op& op, int tw, const PairArgs& a, hipStream_t s, hipEvent_t after_sweep = nullptr,
-                          bool finalize = true, int mode = PAIR_NEWTON, int rows = -1) {
+                          bool finalize = true, int mode = PAIR_NEWTON, int rows = -1, int* nparts = nullptr) {
     if (op.dim == 2) {
         if (rows < 0) rows = op.use_pairs > 1 ? op.use_pairs : 0;
-        return launch_pair2d(op, tw, a, s, after_sweep, finalize, mode, device_cus(), rows);
+        return launch_pair2d(op, tw, a, s, after_sweep, finalize, mode, device_cus(), rows, nparts);
     }
-    return launch_pair(op, tw, a, s, after_sweep, finalize, mode);
+    return launch_pair(op, tw, a, s, after_sweep, finalize, mode, nparts);
 }
 
 #define HIP_TRY(expr)                                                                   \
@@ -308,9 +308,17 @@ int get_hint(Op& op, const DdKey& key) {
     return it == op.degree_hint.end() ? 0 : it->second;
 }
 
+// Degrees differ from substep to substep of a call (later ones start from
+// smoother vectors), so each has a hint of its own; it shares the map through
+// the coefficient count, which is at most kMaxLeja.
+DdKey substep_key(DdKey key, int l) {
+    std::get<4>(key) += (kMaxLeja + 1) * (1 + std::min(l, 63));
+    return key;
+}
+
 void set_hint(Op& op, const DdKey& key, int m) {
     std::lock_guard<std::mutex> lock(op.mu);
-    if (op.degree_hint.size() > 256) op.degree_hint.clear();
+    if (op.degree_hint.size() > 1024) op.degree_hint.clear();
     op.degree_hint[key] = m;
 }
 
@@ -333,6 +341,8 @@ struct LoopOut {
     double fix = 0;       // p holds d_{m+1} w_{m+1} too many (pair stopped at its first product)
     const void* fix_w = nullptr;   // where w_{m+1} is
     bool updated = false;          // the caller's update is already in the stream
+    bool redo = false;             // the loop stopped earlier than the deferred tests can take p back
+                                   // to: run it again with Ctx::defer off
 };
 
 struct Ctx {
@@ -362,7 +372,69 @@ struct Ctx {
     int s_cur = 1, s_min = 1;
     float* features = nullptr;   // device float[8]: features of the prediction
     std::vector<double> di;      // imaginary parts of d (complex operators; else empty)
+    // stop tests of several launches at once where the degree is known from
+    // an earlier loop, and chains of products on 2D stencils; `spare` is
+    // workspace this loop may use for partials besides its own region
+    bool defer = false;
+    bool chains = false;
+    char* spare = nullptr;
+    size_t spare_bytes = 0;
+    int substep = 0;
 };
+
+// Partials of launches whose tests are deferred: each needs a place of its
+// own, taken from the workspace's partials region, then from `spare`.
+struct TestPlan {
+    TestArgs t{};
+    const Ctx& C;
+    size_t used = 0, used_spare = 0, cap;
+    int products = 0;
+    explicit TestPlan(const Ctx& c) : C(c), cap(partials_bytes(*c.op)) {
+        t.st = c.st;
+        t.tol = c.tol;
+        t.roff = -1;
+    }
+    // a place for `bytes` of partials (null: none left)
+    double* place(size_t bytes, int n) {
+        bytes = align256(bytes);
+        if (t.launches >= kMaxTestLaunches || products + n > kMaxTestProducts) return nullptr;
+        if (used + bytes <= cap) {
+            used += bytes;
+            return reinterpret_cast<double*>(reinterpret_cast<char*>(C.partials) + used - bytes);
+        }
+        if (used_spare + bytes <= C.spare_bytes) {
+            used_spare += bytes;
+            return reinterpret_cast<double*>(C.spare + used_spare - bytes);
+        }
+        return nullptr;
+    }
+    void add(const double* part, int nparts, int stride, int off, int n) {
+        t.l[t.launches++] = TestLaunch{part, nparts, stride, off, n};
+        products += n;
+    }
+    // the next places may overwrite these (their tests are in the stream)
+    void clear() {
+        t.launches = 0;
+        products = 0;
+        used = used_spare = 0;
+    }
+};
+
+// Bytes of partials a single product writes at most (one point per lane).
+size_t single_partials(const Op& op) {
+    Tiles t = op.tiles;
+    if (op.kind == 0) t.vec = 1;
+    return (size_t)make_geom(op, t).grid * 4 * sizeof(double);
+}
+
+// Estimate of the degree from the divided differences alone: where their
+// two-term sum falls below the tolerance for terms of the start vector's
+// norm.  Rough inputs stop near it, smooth ones earlier.
+int estimate_degree(const std::vector<double>& d, double tol, int m_max) {
+    for (int m = 2; m <= m_max; ++m)
+        if (std::fabs(d[m - 1]) + std::fabs(d[m]) <= tol * std::fabs(d[0])) return m;
+    return m_max;
+}
 
 // First product reads `src` (storage code tin) and writes w_1 to w0 and p to
 // `p`.  Later products read the buffer holding the latest w and write the
@@ -422,80 +494,217 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     // storage type and alignment the pair sweep reads (w_2 goes to w[0]:
     // `src` may be w[1]).  Otherwise product 0 alone.
     const bool first_pair = C.pairs && C.m_max >= 3 && tin == C.tw && (((uintptr_t)src & 15) == 0);
-    int finalized;
-    int j = 1;
-    if (start_u) {
-        // r and product 0 in one pair sweep (j = -1: its tests are those at
-        // m = 0 and m = 1, and neither can stop)
-        PairArgs b{};
-        b.x = src;
-        b.out = w[0];
+    // With a degree hint, the products up to the last launch before it run
+    // without a test each (their norms are kept) and are tested together:
+    // jd is where the tested launches begin.  Without one, only chains of
+    // products are tested together, up to half the estimated degree.
+    // expected: the degree this substep stopped at last time.  group: the
+    // degree the launches are laid out for.  A stop at the first product of a
+    // pair leaves a rounding of the extra term in p, and pairs and single
+    // products sum their norms in different orders, so 3D pairs are laid out
+    // for the degree of the last loop of this length, whichever substep it
+    // was, and only their tests are deferred.
+    const int expected = get_hint(*C.op, substep_key(C.key, C.substep));
+    const int last_degree = get_hint(*C.op, C.key);
+    const int group = (expected >= 2 && (C.chains || !C.pairs)) ? expected : last_degree;
+    const bool defer_on = C.defer && !C.profile && !C.selector && C.di.empty();
+    const bool chain_first = defer_on && C.chains && !start_u && tin == C.tw && C.m_max >= 6;
+    int jd = 0;
+    bool each = false;   // a test after every deferred launch
+    if (defer_on && expected >= 2 && group >= 2) {
+        const int open = (start_u || !(first_pair || chain_first)) ? 1 : 2;
+        const int end = std::min(group, C.m_max);
+        jd = end - ((C.pairs && (C.chains || (end - open) % 2 == 0)) ? 2 : 1);
+        if (expected < end) jd = std::min(jd, C.pairs ? open + (expected - 1 - open) / 2 * 2 : expected - 1);
+        // (without chains of 5, chains take an even count)
+        if (C.chains && !chain2d_length(*C.op, 5) && (jd - (open == 2 ? 0 : 1)) % 2 != 0) --jd;
+    } else if (defer_on && C.chains) {
+        each = true;
+        const int open = chain_first ? 0 : 1;
+        jd = open + (estimate_degree(d, C.tol, C.m_max) / 2 - open) / 4 * 4;
+    }
+    TestPlan plan(C);
+    int finalized = 0;
+    int j = 0;
+    // the tests of the launches collected so far
+    auto flush = [&]() -> int {
+        if (plan.t.launches == 0) return EXPI_OK;
+        int m = plan.t.m0;
+        int dof = 0;
+        if (plan.t.roff >= 0) plan.t.d[dof++] = std::fabs(d[0]);
+        for (int q = 0; q < plan.products; ++q) plan.t.d[dof + q] = std::fabs(d[m + q]);
+        plan.t.dfix = d[m + plan.products - 1];
+        HIP_TRY(launch_tests(plan.t, C.s));
+        finalized += plan.products;
+        plan.t.m0 = m + plan.products;
+        plan.t.roff = -1;
+        plan.t.cont = 1;
+        plan.clear();
+        return EXPI_OK;
+    };
+    // products j .. j+n-1 as one chain (j = 0: from the start vector), tested
+    // by the next flush; false in *ok when its partials have no place
+    auto chain = [&](int j, int n, bool* ok) -> int {
+        double* part = plan.place(chain2d_partials(*C.op, n, device_cus()), n);
+        *ok = part != nullptr;
+        if (!part) return EXPI_OK;
+        if (plan.t.launches == 0) plan.t.m0 = j + 1;
+        ChainArgs b{};
+        b.first = j == 0;
+        b.x = b.first ? src : w[cur];
+        b.out = b.first ? w[0] : w[cur ^ 1];
         b.p = p;
-        b.partials = C.partials;
+        b.partials = part;
         b.st = C.st;
         b.alpha = 1.0 / C.gamma;
-        b.sigma = 1.0;
-        b.beta2 = -(C.c / C.gamma + C.xi[0]);
-        b.d1 = d[0];
-        b.d2 = d[1];
-        b.tol = C.tol;
-        b.j = -1;
-        b.guard = 0;
-        HIP_TRY(launch_pair(*C.op, C.tw, b, C.s, nullptr, true, PAIR_START));
-        log.push_back({-1, 2, w[0], false});
-        finalized = 1;
-    } else if (first_pair) {
-        PairArgs b{};
-        b.x = src;
-        b.out = w[0];
-        b.p = p;
-        b.partials = C.partials;
-        b.st = C.st;
-        b.alpha = 1.0 / C.gamma;
-        b.beta1 = -(C.c / C.gamma + C.xi[0]);
-        b.beta2 = -(C.c / C.gamma + C.xi[1]);
         b.d0 = d[0];
-        b.d1 = d[1];
-        b.d2 = d[2];
-        b.tol = C.tol;
-        b.j = 0;
-        b.guard = 0;
-        HIP_TRY(launch_pair_op(*C.op, C.tw, b, C.s, nullptr, true, PAIR_FIRST));
-        log.push_back({0, 2, w[0], false});
-        finalized = 2;
+        for (int q = 0; q < n; ++q) {
+            b.beta[q] = -(C.c / C.gamma + C.xi[j + q]);
+            b.d[q] = d[j + q + 1];
+        }
+        b.guard = plan.t.cont;
+        int np = 0;
+        HIP_TRY(launch_chain2d(*C.op, C.tw, n, b, device_cus(), &np, C.s));
+        if (b.first) plan.t.roff = 0;
+        else cur ^= 1;
+        plan.add(part, np, 16, 1, n);
+        plan.t.pair_last = n == 2;
+        plan.t.outbuf = cur;
+        log.push_back({j, n, w[cur], false});
+        return EXPI_OK;
+    };
+    // Pairs of a constant-coefficient 2D stencil are chains of two (FP64): a
+    // product then rounds the same however the launches are grouped.
+    const bool chain_pairs = C.chains && C.pairs && !C.profile && !C.selector;
+    const bool chain_open = chain_first && jd >= 4;
+    if (!chain_open && chain_pairs && first_pair) {
+        bool ok = true;
+        int rc = chain(0, 2, &ok);
+        if (rc) return rc;
+        if (!ok) return fail(EXPI_EHIP, "internal: no room for a chain's partials");
         j = 2;
-    } else {
-        HIP_TRY(launch_sweep(*C.op, EPI_FIRST, tin, C.tw, a, C.s));
-        log.push_back({0, 1, w[0], false});
-        finalized = 1;
+        if (jd <= 2) rc = flush();
+        if (rc) return rc;
+    } else if (!chain_open) {
+        double* part0 = C.partials;
+        bool fin0 = true;
+        if (jd > 2) {
+            // the opening launch joins the deferred tests
+            part0 = plan.place(!(start_u || first_pair) ? single_partials(*C.op)
+                               : C.op->dim == 2         ? pair2d_partials(*C.op)
+                                                        : (size_t)pair_geom(*C.op, device_cus()).grid * 64,
+                               2);
+            fin0 = part0 == nullptr;
+            if (!part0) part0 = C.partials;
+        }
+        a.partials = part0;
+        int np = 0;
+        if (start_u) {
+            // r and product 0 in one pair sweep (j = -1: its tests are those at
+            // m = 0 and m = 1, and neither can stop)
+            PairArgs b{};
+            b.x = src;
+            b.out = w[0];
+            b.p = p;
+            b.partials = part0;
+            b.st = C.st;
+            b.alpha = 1.0 / C.gamma;
+            b.sigma = 1.0;
+            b.beta2 = -(C.c / C.gamma + C.xi[0]);
+            b.d1 = d[0];
+            b.d2 = d[1];
+            b.tol = C.tol;
+            b.j = -1;
+            b.guard = 0;
+            HIP_TRY(launch_pair(*C.op, C.tw, b, C.s, nullptr, fin0, PAIR_START, &np));
+            log.push_back({-1, 2, w[0], false});
+            j = 1;
+            if (!fin0) plan.add(part0, np, 4, 0, 2);
+            else finalized = 1;
+        } else if (first_pair) {
+            PairArgs b{};
+            b.x = src;
+            b.out = w[0];
+            b.p = p;
+            b.partials = part0;
+            b.st = C.st;
+            b.alpha = 1.0 / C.gamma;
+            b.beta1 = -(C.c / C.gamma + C.xi[0]);
+            b.beta2 = -(C.c / C.gamma + C.xi[1]);
+            b.d0 = d[0];
+            b.d1 = d[1];
+            b.d2 = d[2];
+            b.tol = C.tol;
+            b.j = 0;
+            b.guard = 0;
+            HIP_TRY(launch_pair_op(*C.op, C.tw, b, C.s, nullptr, fin0, PAIR_FIRST, -1, &np));
+            log.push_back({0, 2, w[0], false});
+            j = 2;
+            plan.t.m0 = 1;
+            plan.t.roff = 0;
+            if (!fin0) plan.add(part0, np, 8, 1, 2);
+            else finalized = 2;
+        } else {
+            HIP_TRY(launch_sweep(*C.op, EPI_FIRST, tin, C.tw, a, C.s, nullptr, fin0, &np));
+            log.push_back({0, 1, w[0], false});
+            j = 1;
+            plan.t.m0 = 1;
+            plan.t.roff = 0;
+            if (!fin0) plan.add(part0, np, 4, 1, 1);
+            else finalized = 1;
+        }
+        a.partials = C.partials;
+        if (fin0) {
+            // tested already: deferred launches, if any, go on from its state
+            plan.clear();
+            plan.t.m0 = j + 1;
+            plan.t.roff = -1;
+            plan.t.cont = 1;
+            if (!C.chains || !each) jd = 0;
+        }
     }
 
     // single product j (j >= 1); `fin` adds the norm reduction and stop test
-    auto single = [&](int j, bool fin) -> int {
+    // (with `part`, the launch leaves its norms there for the deferred tests)
+    auto single = [&](int j, bool fin, double* part = nullptr) -> int {
+        int np = 0;
+        a.partials = part ? part : C.partials;
         a.x = w[cur];
         a.out = w[cur ^ 1];
         a.j = j;
         a.beta = -(C.c / C.gamma + C.xi[j]);
         a.d1 = d[j + 1];
         if (!C.di.empty()) a.d1i = C.di[j + 1];
-        a.guard = 1;
+        a.guard = (part && !plan.t.cont) ? 0 : 1;
         a.tol = tol_now;
         const bool tm = timing();
         if (tm) HIP_TRY(hipEventRecord(tl_ctx.tev[2 * j], C.s));
         HIP_TRY(launch_sweep(*C.op, EPI_NEWTON, C.tw, C.tw, a, C.s, tm ? tl_ctx.tev[2 * j + 1] : nullptr,
-                             fin));
+                             fin && !part, &np));
+        if (part) {
+            plan.add(part, np, 4, 1, 1);
+            plan.t.pair_last = 0;
+        }
         log.push_back({j, 1, w[cur ^ 1], tm});
         cur ^= 1;
-        if (fin) ++finalized;
+        if (fin && !part) ++finalized;
         return EXPI_OK;
     };
     // products j and j+1 in one pair sweep
-    auto pair = [&](int j, bool fin) -> int {
+    auto pair = [&](int j, bool fin, double* part = nullptr) -> int {
+        if (chain_pairs) {
+            bool ok = true;
+            const int rc = chain(j, 2, &ok);
+            if (rc) return rc;
+            if (!ok) return fail(EXPI_EHIP, "internal: no room for a chain's partials");
+            return fin ? flush() : EXPI_OK;
+        }
+        int np = 0;
         PairArgs b{};
         b.x = w[cur];
         b.out = w[cur ^ 1];
         b.p = p;
-        b.partials = C.partials;
+        b.partials = part ? part : C.partials;
         b.st = C.st;
         b.alpha = 1.0 / C.gamma;
         b.beta1 = -(C.c / C.gamma + C.xi[j]);
@@ -504,14 +713,20 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         b.d2 = d[j + 2];
         b.tol = tol_now;
         b.j = j;
-        b.guard = 1;
+        b.guard = (part && !plan.t.cont) ? 0 : 1;
         b.outbuf = cur ^ 1;
         const bool tm = timing();
         if (tm) HIP_TRY(hipEventRecord(tl_ctx.tev[2 * j], C.s));
-        HIP_TRY(launch_pair_op(*C.op, C.tw, b, C.s, tm ? tl_ctx.tev[2 * j + 1] : nullptr, fin));
+        HIP_TRY(launch_pair_op(*C.op, C.tw, b, C.s, tm ? tl_ctx.tev[2 * j + 1] : nullptr,
+                               fin && !part, PAIR_NEWTON, -1, &np));
+        if (part) {
+            plan.add(part, np, 4, 0, 2);
+            plan.t.pair_last = 1;
+            plan.t.outbuf = cur ^ 1;
+        }
         log.push_back({j, 2, w[cur ^ 1], tm});
         cur ^= 1;
-        if (fin) finalized += 2;
+        if (fin && !part) finalized += 2;
         return EXPI_OK;
     };
     // `count` products from j on (pairs where allowed), advancing j; the
@@ -548,6 +763,56 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         if (rc) return rc;
         return wait_slot(slot, st);
     };
+
+    // the deferred part: products up to jd
+    while (j < jd) {
+        int rc;
+        bool ok = true;
+        const int left = jd - j;
+        if (C.chains) {
+            // (const coefficient: 6, then 5 or 4 so that what is left is no
+            // single product, and a pair for a remainder of 2; else 4 and 2)
+            int n = 0;
+            const bool six = !each && chain2d_length(*C.op, 6);
+            if (six && left >= 6 && left != 8 && left != 7 && left != 9) n = 6;
+            else if (six && (left == 5 || left == 7 || left == 9)) n = 5;
+            else if (left >= 4) n = 4;
+            else if (left >= 2 && j > 0) n = 2;
+            if (n) {
+                rc = chain(j, n, &ok);
+                if (rc) return rc;
+                if (ok) j += n;
+                if (ok && each) rc = flush();
+                if (rc) return rc;
+                if (ok) continue;
+                // no place left: test what there is, which frees all places
+                if (plan.t.launches == 0) break;
+                rc = flush();
+                if (rc) return rc;
+                continue;
+            }
+        }
+        if (each) break;
+        const bool two = C.pairs && left >= 2;
+        const size_t bytes = !two ? single_partials(*C.op)
+                             : C.op->dim == 2 ? pair2d_partials(*C.op)
+                                              : (size_t)pair_geom(*C.op, device_cus()).grid * 32;
+        double* part = plan.place(bytes, two ? 2 : 1);
+        if (!part) {
+            if (plan.t.launches == 0) break;
+            rc = flush();
+            if (rc) return rc;
+            continue;
+        }
+        rc = two ? pair(j, false, part) : single(j, false, part);
+        if (rc) return rc;
+        j += two ? 2 : 1;
+    }
+    {
+        const int rc = flush();
+        if (rc) return rc;
+    }
+    a.partials = C.partials;
 
     NewtonState last{};
     bool finished = false;
@@ -628,7 +893,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     }
 
     if (!finished) {
-        const int hint = learned_tail ? 0 : get_hint(*C.op, C.key);
+        const int hint = learned_tail ? 0 : group;
         // With a degree hint (or after a prediction) the first batch ends at
         // the expected stop and later batches are one launch; without one,
         // batches of 4 then 2 products run one batch ahead of the status
@@ -665,6 +930,10 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         }
         out->updated = spec && !ahead && last.done == 1;
     }
+    if (last.done == 3) {
+        out->redo = true;
+        return EXPI_OK;
+    }
     out->m = last.m;
     out->done = last.done;
     out->err = last.err;
@@ -678,13 +947,17 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         if (!out->fix_w) return fail(EXPI_EHIP, "internal: no pair sweep for the stop at m");
         out->fix = last.fix;
     }
-    if (last.done == 1) set_hint(*C.op, C.key, last.m);
+    if (last.done == 1) {
+        set_hint(*C.op, C.key, last.m);
+        set_hint(*C.op, substep_key(C.key, C.substep), last.m);
+    }
     if (last.done != 2) {
         // launches that began before the stop did work (the opening ones
         // always do); later ones returned at once
         for (const Launch& L : log) {
             if (L.j >= last.m && L.j > 0) continue;
-            if (L.n == 2) ++out->pair_launches;
+            // (a chain counts its products two by two)
+            if (L.n >= 2) out->pair_launches += L.n / 2;
             else ++out->single_launches;
         }
     }
@@ -778,8 +1051,9 @@ int validate_call(const expi_op* op, double tau, double tol, int dtype, void* ws
 void set_error(const std::string& msg) { tl_error = msg; }
 
 // ---- phi_action -------------------------------------------------------------------
+// y_slot: whether the layout's y slot is free for this call.
 static int run_phi(Op& op, int k, double tau, const double* v, double* y, double tol, int dtype,
-                   const Params& P, char* ws, expi_stats* st, hipStream_t s) {
+                   const Params& P, char* ws, expi_stats* st, hipStream_t s, bool y_slot = true) {
     double ia, ib;
     int rc = common_setup(op, tau, tol, dtype, P, ws, s, &ia, &ib);
     if (rc) return rc;
@@ -804,7 +1078,7 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
         acc.interval_a = ia;
         acc.interval_b = ib;
         HIP_TRY(launch_reset(C.st, s));
-        bool ok = true;
+        bool ok = true, again = false;
         for (int l = 0; l < sub && ok; ++l) {
             // p goes straight into y when y is the result and has p's type
             const bool p_in_y = (sub == 1 && tw == 0);
@@ -871,6 +1145,14 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
             }
             LoopOut lo;
             C.pairs = P.pairs && pairs_on(op, tw) && (((uintptr_t)p & 15) == 0);
+            C.chains = P.pairs && op.use_pairs != 0 && chain2d_supported(op, tw);
+            C.spare = y_slot ? ws + L.y : nullptr;
+            C.spare_bytes = y_slot ? (size_t)n * 8 : 0;
+            // (a substep of phi_k, k >= 2, adds to y while it forms its start
+            // vector, so it cannot be run again)
+            C.defer = !again && !(phik_sub && l > 0);
+            C.substep = l;
+            again = false;
             // the update of this substep, enqueued ahead of the status
             // read-back where it always runs (p_in_y needs one only for a fix)
             const double* yin = ((k == 1 || phik_sub) && l > 0) ? y : nullptr;
@@ -880,6 +1162,13 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
             };
             rc = newton_loop(C, src, tin, p, &lo, false, p_in_y ? nullptr : &spec);
             if (rc) return rc;
+            if (lo.redo) {
+                // the same substep with a stop test per launch
+                if (k == 1 && l > 0) acc.matvecs -= 1;
+                again = true;
+                --l;
+                continue;
+            }
             stats_add(&acc, lo);
             if (lo.done == 2) return fail(EXPI_ENONFINITE, "a norm became inf/NaN (non-finite input?)");
             if (lo.done != 1) {
@@ -965,7 +1254,7 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
         acc.interval_a = ia;
         acc.interval_b = ib;
         HIP_TRY(launch_reset(C.st, s));
-        bool ok = true;
+        bool ok = true, again = false;
         int restart = 0;
         for (int l = 0; l < sub && ok; ++l) {
             // r = A y_l + g(u), y_0 = u: its own sweep, or (first substep)
@@ -988,6 +1277,12 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
                 return launch_update_st(n, yout, yin, p, tw, delta, C.st, ws + L.w0, ws + L.w1, s);
             };
             LoopOut lo;
+            C.chains = P.pairs && op.use_pairs != 0 && chain2d_supported(op, tw);
+            C.spare = sub == 1 ? ws + L.y : nullptr;   // y_l lives there otherwise
+            C.spare_bytes = sub == 1 ? (size_t)n * 8 : 0;
+            C.defer = !again;
+            C.substep = l;
+            again = false;
             if (fuse) {
                 rc = newton_loop(C, u, 0, p, &lo, true, &spec);
                 acc.fused_starts += 1;
@@ -1004,6 +1299,14 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
                 rc = newton_loop(C, ws + L.w1, tw, p, &lo, false, &spec);
             }
             if (rc) return rc;
+            if (lo.redo) {
+                // the same substep with a stop test per launch
+                acc.matvecs -= 1;
+                if (fuse) acc.fused_starts -= 1;
+                again = true;
+                --l;
+                continue;
+            }
             if (lo.restart_s) {
                 // the probe predicts fewer substeps: its products are spent
                 restart = lo.restart_s;
@@ -1155,7 +1458,7 @@ static int run_exprk2(Op& op, int nonlin, double tau, double* u, double tol, int
         return rc;
     }
     HIP_TRY(launch_gdiff(nonlin, n, u, un, dg, s));
-    rc = run_phi(op, 2, tau, dg, un, tol, dtype, P, ws, &s2, s);
+    rc = run_phi(op, 2, tau, dg, un, tol, dtype, P, ws, &s2, s, false);
     expi_stats acc = s1;
     acc.substeps = std::max(s1.substeps, s2.substeps);
     acc.newton_steps += s2.newton_steps;

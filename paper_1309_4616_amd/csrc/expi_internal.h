@@ -24,7 +24,8 @@ constexpr int kMaxPairWaves = 16;   // waves of a pair-sweep workgroup
 // ---------------------------------------------------------------------------
 struct alignas(64) NewtonState {
     unsigned int arrive;  // reserved
-    int done;             // 0 running, 1 stop test met, 2 non-finite norm
+    int done;             // 0 running, 1 stop test met, 2 non-finite norm, 3 stop test met earlier than p
+                          // can be taken back to (deferred tests): run the loop again
     int m;                // products taken in this loop
     int fixbuf;           // with fix: which of the two w buffers holds w_{m+1}
     double t_prev;        // |d_m| ||w_m|| of the latest product
@@ -129,6 +130,57 @@ struct PairGeom {
     int nxw, rows, nrt, chunk, grid, per_xcd;
 };
 
+// Arguments of a chain sweep: T = 2, 4, 5 or 6 consecutive Newton products of a
+// 2D stencil in one pass (chain2d.h).
+constexpr int kMaxChain = 6;
+struct ChainArgs {
+    const void* x;        // w_j
+    void* out;            // w_{j+T}
+    void* p;              // running Newton sum, p_j in, p_{j+T} out
+    const double* tx;     // separable coefficient tables
+    const double* ty;
+    const double* field;  // coefficient field
+    double* partials;     // [grid][16]: ||w_j||^2 or ||p_j||^2, then ||w||^2, ||p||^2 per product
+    NewtonState* st;
+    double alpha, beta[kMaxChain];   // beta_j .. beta_{j+T-1}
+    double d0, d[kMaxChain];         // d_{j+1} .. d_{j+T}; d0 with `first`
+    double ih2[2], hpos[2], c0ih[2], c0, c1;
+    int n[2];
+    int bc;
+    int guard;
+    int first;            // the chain opens the loop: p_j = d_0 w_0, nothing read from p
+    int march, tiles0, ntiles;
+};
+
+struct ChainShape {
+    int vec, tiles0, march, ntiles, grid;
+    bool stream;          // streaming stores, strips on whole cache lines
+};
+
+// The stop tests of several launches at once (sweep.hip): per launch where
+// its partials are and which products it took.
+constexpr int kMaxTestLaunches = 48;
+constexpr int kMaxTestProducts = 128;
+struct TestLaunch {
+    const double* part;
+    int nparts, stride;   // workgroups; doubles per workgroup
+    int off;              // ||w||^2 of the launch's first product among them (then ||p||^2, ...)
+    int n;                // products
+};
+struct TestArgs {
+    TestLaunch l[kMaxTestLaunches];
+    double d[kMaxTestProducts + 1];   // |d_m| of the products tested, from degree m0 on
+    NewtonState* st;
+    NewtonState* mirror;
+    double tol;
+    double dfix;          // with pair_last: d (signed) of the last product
+    int launches, m0;     // m0: degree reached by the first product (0: the norm of the start vector)
+    int roff;             // place of ||r||^2 among the first launch's partials (-1: it is ||w|| of degree m0 = 0)
+    int pair_last;        // the last launch is a pair sweep: a stop at its first product is correctable
+    int outbuf;           // w buffer that launch writes
+    int cont;             // products tested before these: go on from the state's t, do nothing once stopped
+};
+
 // Arguments of the one-workgroup finalize kernel that follows a reducing sweep.
 struct FinalArgs {
     const double* partials;
@@ -216,11 +268,13 @@ size_t partials_bytes(const Op& op);
 
 // Launchers.  TIN/TOUT codes: 0 = double, 1 = float.  launch_sweep picks the
 // geometry from op.tiles and adds the finalize kernel after reducing sweeps.
+// `nparts`, if given, receives the workgroups that wrote partials (here and in
+// the pair sweeps).
 // `after_sweep`, if given, is recorded on `s` between the sweep and its
 // finalize kernel (profiling of the sweep alone).
 hipError_t launch_sweep(const Op& op, int epi, int tin, int tout, SweepArgs a,
                         hipStream_t s, hipEvent_t after_sweep = nullptr,
-                        bool finalize = true);
+                        bool finalize = true, int* nparts = nullptr);
 hipError_t launch_stencil(const Op& op, const Geom& g, int epi, int tin, int tout,
                           const SweepArgs& a, hipStream_t s);
 hipError_t launch_csr(const Geom& g, int epi, int tin, int tout, const SweepArgs& a,
@@ -253,10 +307,23 @@ PairGeom pair_geom(const Op& op, int cus);
 // (the finalize records t_0, t_1 and ||r||, and cannot stop at m = 1).
 hipError_t launch_pair(const Op& op, int tw, PairArgs a, hipStream_t s,
                        hipEvent_t after_sweep = nullptr, bool finalize = true,
-                       int mode = PAIR_NEWTON);
+                       int mode = PAIR_NEWTON, int* nparts = nullptr);
 hipError_t launch_pair_finalize(const double* partials, NewtonState* st, int nparts, int j,
                                 int guard, double d0, double d1, double d2, double tol, int mode,
                                 int outbuf, hipStream_t s);
+// Chain sweeps of 2D stencils (chain2d.h): n products from a.x, partials of
+// *nparts workgroups (16 doubles each) at a.partials, no finalize.
+bool chain2d_supported(const Op& op, int tw);
+bool chain2d_length(const Op& op, int n);
+hipError_t launch_chain2d(const Op& op, int tw, int n, ChainArgs a, int cus, int* nparts, hipStream_t s);
+// Bytes of partials a chain sweep of n products writes at most.
+size_t chain2d_partials(const Op& op, int n, int cus);
+size_t pair2d_partials(const Op& op);
+// The stop tests of the launches in `t`, in order of their products: the
+// state as the finalize kernels of the launches would have left it.  A stop
+// that leaves later terms in p (other than the one a pair sweep leaves) is
+// recorded as done = 3: the loop has to be run again with a test per launch.
+hipError_t launch_tests(TestArgs& t, hipStream_t s);
 hipError_t launch_fill(void* out, int64_t n, int t, double scale, hipStream_t s);
 // The boundary term of a stencil's Dirichlet data over its boundary layer
 // (boundary.hip): y += scale * b_f, y of storage code t.

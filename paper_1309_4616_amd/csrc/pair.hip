@@ -246,27 +246,6 @@ __device__ __forceinline__ double uniform(double v) {
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// Whole-wave shifts by one lane through DPP: lane l receives `src` of lane
-// l-1 (from_left) or l+1 (from_right); the lane without a source (0, resp.
-// 63) keeps `edge`.
-template <int CTRL>
-__device__ __forceinline__ float dpp_shift(float edge, float src) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, edge),
-                                                                 __builtin_bit_cast(int, src), CTRL,
-                                                                 0xF, 0xF, false));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_shift(double edge, double src) {
-    const unsigned long long e = __builtin_bit_cast(unsigned long long, edge);
-    const unsigned long long v = __builtin_bit_cast(unsigned long long, src);
-    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)e, (int)(unsigned)v, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(e >> 32), (int)(unsigned)(v >> 32), CTRL,
-                                               0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-constexpr int kDppWaveShr1 = 0x138;   // lane l <- lane l-1
-constexpr int kDppWaveShl1 = 0x130;   // lane l <- lane l+1
-
 // MODE (PairMode).  PAIR_FIRST: the pair starts the loop.  It reads the
 // start vector r (= w_0), forms p_1 = d_0 r + d_1 w_1 instead of adding to
 // a stored p, and reports
@@ -801,7 +780,7 @@ int device_cus() {
 }
 
 hipError_t launch_pair(const Op& op, int tw, PairArgs a, hipStream_t s, hipEvent_t after_sweep,
-                       bool finalize, int mode) {
+                       bool finalize, int mode, int* nparts) {
     if (mode == PAIR_START && !pair_start_supported(op)) return hipErrorInvalidValue;
     const PairGeom g = pair_geom(op, device_cus());
     for (int d = 0; d < 3; ++d) {
@@ -821,6 +800,7 @@ hipError_t launch_pair(const Op& op, int tw, PairArgs a, hipStream_t s, hipEvent
     a.nrt = g.nrt;
     a.chunk = g.chunk;
     a.per_xcd = g.per_xcd;
+    if (nparts) *nparts = g.grid;
     hipError_t e;
     if (mode == PAIR_START)
         e = tw == 1 ? go<float, PAIR_START>(g, op.coef, op.bc, a, s) : go<double, PAIR_START>(g, op.coef, op.bc, a, s);

@@ -282,10 +282,17 @@ bool pair2d_supported(const Op& op, int tw) {
            op.size * 8 < ((int64_t)1 << 31) - 64;
 }
 
+// Bytes of partials a pair sweep writes at most (smallest tiles).
+size_t pair2d_partials(const Op& op) {
+    const int64_t tiles = (int64_t)((op.n[0] + 63) / 64) * ((op.n[1] + 3) / 4);
+    const int64_t wgs = (tiles + kP2Waves - 1) / kP2Waves;
+    return (size_t)std::min<int64_t>(kP2MaxGrid, (wgs + kXcd - 1) / kXcd * kXcd) * 8 * sizeof(double);
+}
+
 // rows: rows per tile (pair2d_rows_valid), or 0 for 16, fewer where the
 // grid has too few tiles of 16 rows.
 hipError_t launch_pair2d(const Op& op, int tw, PairArgs a, hipStream_t s, hipEvent_t after_sweep, bool finalize,
-                         int mode, int cus, int rows) {
+                         int mode, int cus, int rows, int* nparts) {
     if (mode != PAIR_NEWTON && mode != PAIR_FIRST) return hipErrorInvalidValue;
     if (rows != 0 && !pair2d_rows_valid(rows)) return hipErrorInvalidValue;
     for (int d = 0; d < 2; ++d) {
@@ -311,6 +318,7 @@ hipError_t launch_pair2d(const Op& op, int tw, PairArgs a, hipStream_t s, hipEve
     // a multiple of the XCD count
     const int want = std::min((ntiles + kP2Waves - 1) / kP2Waves, 4 * std::max(cus, kXcd));
     const int grid = std::min(kP2MaxGrid, std::max(kXcd, (want + kXcd - 1) / kXcd * kXcd));
+    if (nparts) *nparts = grid;
     hipError_t e;
     if (mode == PAIR_FIRST)
         e = tw == 1 ? go2<float, PAIR_FIRST>(vec, grid, tiles0, ntiles, march, a, s)

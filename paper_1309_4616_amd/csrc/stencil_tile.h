@@ -30,12 +30,6 @@ __device__ __forceinline__ TC boundary_value(int kind, TC x, TC y, TC z) {
         return sin(3.14159265358979323846 * z) * exp(-x * y);
 }
 
-// D(x, y) = 1/sqrt(1 + x^2 + y^2) of Sec. III-B
-template <class TC>
-__device__ __forceinline__ TC d_coefficient(TC x, TC y) {
-    return (TC)1 / sqrt((TC)1 + x * x + y * y);
-}
-
 template <int V, class T, class TC>
 __device__ __forceinline__ void vld(const T* __restrict__ p, int idx, TC (&o)[V]) {
     if constexpr (V == 2) {

@@ -147,6 +147,113 @@ __global__ __launch_bounds__(kFinalThreads) void pair_finalize_kernel(FinalArgs 
     mirror_state(f);
 }
 
+// Stop tests of several launches at once (TestArgs): the sums of every
+// launch's partials first, one (launch, value) per wave at a time in a fixed
+// order, then the two-term test of every product in order of degree.  One
+// such kernel takes the place of a finalize kernel after each launch (5 us
+// and a gap of 2 us on the stream each).
+constexpr int kTestThreads = 1024;
+constexpr int kMaxTestValues = 2 * kMaxTestProducts + 1;
+__global__ __launch_bounds__(kTestThreads) void tests_kernel(TestArgs f) {
+    __shared__ double sum[kMaxTestValues];
+    __shared__ double wns[kMaxTestProducts], pns[kMaxTestProducts], ts[kMaxTestProducts];
+    __shared__ int first_stop;
+    NewtonState* st = f.st;
+    if (f.cont && f.st->done != 0) {   // the same in every thread
+        FinalArgs g{};
+        g.st = f.st;
+        g.mirror = f.mirror;
+        mirror_state(g);
+        return;
+    }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int nw = kTestThreads / 64;
+    const double tprev_in = f.cont ? f.st->t_prev : 0.0;
+    const int lead = f.roff >= 0 ? 1 : 0;   // ||r||^2 comes before the products' values
+    int base = 0;                           // first value of the launch among the sums
+    for (int q = 0; q < f.launches; ++q) {
+        const TestLaunch& L = f.l[q];
+        const int ld = q == 0 ? lead : 0;
+        const int nv = 2 * L.n + ld;
+        for (int v = (wv - base % nw + nw) % nw; v < nv; v += nw) {
+            const double* part = L.part + ((ld && v == 0) ? f.roff : L.off + v - ld);
+            // in the order of the finalize kernels (256 threads, four waves),
+            // whose sums these equal bit for bit; eight loads in flight,
+            // clamped ones count zero
+            static_assert(kFinalThreads == 256, "four partial sums per lane");
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int b0 = lane; b0 < L.nparts; b0 += 512) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = part[(size_t)L.stride * min(b0 + 64 * u, L.nparts - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc[u & 3] += (b0 + 64 * u < L.nparts) ? x[u] : 0.0;
+            }
+            double s = wave_sum(acc[0]);
+#pragma unroll
+            for (int u = 1; u < 4; ++u) s += wave_sum(acc[u]);
+            if (lane == 0) sum[base + v] = s;
+        }
+        base += nv;
+    }
+    __syncthreads();
+    // one product per thread: its norms, its term and its two-term test
+    const int total = (base - lead) / 2;
+    const int q = (int)threadIdx.x;
+    if (q < total) {
+        wns[q] = sqrt(sum[lead + 2 * q]);
+        pns[q] = sqrt(sum[lead + 2 * q + 1]);
+        ts[q] = f.d[lead + q] * wns[q];
+    }
+    if (q == 0) first_stop = total;
+    __syncthreads();
+    double tprev = tprev_in;
+    int done = 0;
+    if (q < total) {
+        if (q > 0) tprev = ts[q - 1];
+        else if (lead) tprev = f.d[0] * sqrt(sum[0]);
+        const int m = f.m0 + q;
+        if (m < kHist) st->hist[m] = ts[q];   // (terms past a stop are not looked at)
+        if (!isfinite(wns[q]) || !isfinite(pns[q]) || !isfinite(tprev)) done = 2;
+        else if (m >= 2 && tprev + ts[q] <= f.tol * pns[q]) done = 1;
+        if (done) atomicMin(&first_stop, q);
+    }
+    __syncthreads();
+    const int stop = min(first_stop, total - 1);
+    if (q != stop) return;
+    if (lead) {
+        st->rnorm = sqrt(sum[0]);
+        st->hist[0] = f.d[0] * sqrt(sum[0]);
+    } else if (f.m0 == 0) {
+        st->rnorm = wns[0];
+    }
+    const double wn = wns[q], pn = pns[q], num = tprev + ts[q];
+    const int left = total - 1 - q;     // products taken past the stop
+    double fix = 0.0;
+    if (done == 1 && left > 0) {
+        if (left == 1 && f.pair_last) {
+            fix = f.dfix;
+            st->fixbuf = f.outbuf;
+        } else {
+            done = 3;
+        }
+    }
+    st->fix = fix;
+    st->t_prev = ts[q];
+    st->err = (pn > 0.0) ? num / pn : (num == 0.0 ? 0.0 : INFINITY);
+    st->pnorm = pn;
+    st->wnorm = wn;
+    st->m = f.m0 + q;
+    st->done = done;
+    if (f.mirror != nullptr) {
+        // (this thread wrote the record; thread 0 is the mirror's writer
+        // elsewhere)
+        const unsigned long long* from = reinterpret_cast<const unsigned long long*>(st);
+        unsigned long long* to = reinterpret_cast<unsigned long long*>(f.mirror);
+        for (int w = 0; w < (int)(sizeof(NewtonState) / 8); ++w) to[w] = from[w];
+    }
+}
+
 __global__ void reset_kernel(NewtonState* st) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         st->arrive = 0;
@@ -260,7 +367,7 @@ size_t partials_bytes(const Op& op) {
 }
 
 hipError_t launch_sweep(const Op& op, int epi, int tin, int tout, SweepArgs a, hipStream_t s,
-                        hipEvent_t after_sweep, bool finalize) {
+                        hipEvent_t after_sweep, bool finalize, int* nparts) {
     Tiles t = op.tiles;
     if (op.kind == 0 && t.vec == 2) {
         // 16-byte vector accesses need an even row length and aligned arrays
@@ -273,6 +380,7 @@ hipError_t launch_sweep(const Op& op, int epi, int tin, int tout, SweepArgs a, h
     a.ntiles = g.ntiles;
     a.per_xcd = g.per_xcd;
     a.march = g.march;
+    if (nparts) *nparts = g.grid;
     hipError_t e;
     if (op.kind != 0) {
         a.n[0] = (int)op.nrows;
@@ -377,6 +485,15 @@ hipError_t launch_pair_finalize(const double* partials, NewtonState* st, int npa
     f.d2 = d2;
     f.tol = tol;
     hipLaunchKernelGGL(pair_finalize_kernel, dim3(1), dim3(kFinalThreads), 0, s, f);
+    return hipGetLastError();
+}
+
+hipError_t launch_tests(TestArgs& t, hipStream_t s) {
+    int total = 0;
+    for (int q = 0; q < t.launches; ++q) total += t.l[q].n;
+    if (t.launches < 1 || t.launches > kMaxTestLaunches || total > kMaxTestProducts) return hipErrorInvalidValue;
+    t.mirror = tl_mirror;
+    hipLaunchKernelGGL(tests_kernel, dim3(1), dim3(kTestThreads), 0, s, t);
     return hipGetLastError();
 }
 

@@ -192,6 +192,46 @@ __device__ inline void pair_tests(const FinalArgs& f) {
     st->done = done;
 }
 
+// Whole-wave shifts by one lane through DPP: lane l receives `src` of lane
+// l-1 (from_left) or l+1 (from_right); the lane without a source (0, resp.
+// 63) keeps `edge`.
+template <int CTRL>
+__device__ __forceinline__ float dpp_shift(float edge, float src) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, edge),
+                                                                 __builtin_bit_cast(int, src), CTRL,
+                                                                 0xF, 0xF, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift(double edge, double src) {
+    const unsigned long long e = __builtin_bit_cast(unsigned long long, edge);
+    const unsigned long long v = __builtin_bit_cast(unsigned long long, src);
+    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)e, (int)(unsigned)v, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(e >> 32), (int)(unsigned)(v >> 32), CTRL,
+                                               0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+// The same with 0 for the lane without a source (no register to set first).
+template <int CTRL>
+__device__ __forceinline__ float dpp_shift0(float src) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, src), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift0(double src) {
+    const unsigned long long v = __builtin_bit_cast(unsigned long long, src);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)v, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(v >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+constexpr int kDppWaveShr1 = 0x138;   // lane l <- lane l-1
+constexpr int kDppWaveShl1 = 0x130;   // lane l <- lane l+1
+
+// D(x, y) = 1/sqrt(1 + x^2 + y^2) of Sec. III-B
+template <class TC>
+__device__ __forceinline__ TC d_coefficient(TC x, TC y) {
+    return (TC)1 / sqrt((TC)1 + x * x + y * y);
+}
+
 // Face weight of the face of cell c towards a neighbour with coefficient
 // anb: the mean of the two coefficients if the neighbour exists; for a
 // missing neighbour the cell's own coefficient under homogeneous Dirichlet
