@@ -377,6 +377,7 @@ struct Ctx {
     // workspace this loop may use for partials besides its own region
     bool defer = false;
     bool chains = false;
+    bool resident = false;   // the whole loop in one workgroup
     char* spare = nullptr;
     size_t spare_bytes = 0;
     int substep = 0;
@@ -452,6 +453,39 @@ int estimate_degree(const std::vector<double>& d, double tol, int m_max) {
 int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool start_u = false,
                 const std::function<hipError_t()>* spec = nullptr) {
     const std::vector<double>& d = C.d;
+    if (C.resident && tin == 0) {
+        // the whole loop in one launch
+        ResidentArgs r{};
+        r.x = static_cast<const double*>(src);
+        r.p = static_cast<double*>(p);
+        r.st = C.st;
+        r.tol = C.tol;
+        r.m_max = C.m_max;
+        for (int q = 0; q <= C.m_max; ++q) r.d[q] = d[q];
+        for (int q = 0; q < C.m_max; ++q) r.beta[q] = -(C.c / C.gamma + C.xi[q]);
+        int slot;
+        int rc = mirror_begin(&slot);
+        if (rc) return rc;
+        r.mirror = tl_ctx.pinned_dev + slot;
+        HIP_TRY(launch_resident2d(*C.op, r, 1.0 / C.gamma, C.s));
+        rc = mirror_end(slot, C.s);
+        if (rc) return rc;
+        if (spec) HIP_TRY((*spec)());
+        NewtonState h;
+        rc = wait_slot(slot, &h, C.st);
+        if (rc) return rc;
+        out->m = h.m;
+        out->done = h.done;
+        out->err = h.err;
+        out->rnorm = h.rnorm;
+        for (int q = 0; q < kHist; ++q) out->hist[q] = h.hist[q];
+        out->finalized = h.m;
+        out->updated = spec && h.done == 1;
+        out->pair_launches = h.m / 2;   // products counted two by two
+        out->single_launches = h.m % 2;
+        if (h.done == 1) set_hint(*C.op, C.key, h.m);
+        return EXPI_OK;
+    }
     void* w[2] = {C.ws + C.L.w0, C.ws + C.L.w1};
     // tolerance of the stop tests of the launches enqueued next; 0 makes a
     // finalize record the norms and the latest term t_m without stopping
@@ -1077,7 +1111,10 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
         acc.retries = attempt;
         acc.interval_a = ia;
         acc.interval_b = ib;
-        HIP_TRY(launch_reset(C.st, s));
+        // (a loop in one workgroup writes the whole record itself)
+        C.chains = P.pairs && op.use_pairs != 0 && chain2d_supported(op, tw);
+        C.resident = C.chains && !P.profile && !P.selector && resident2d_supported(op, tw, P.m_max);
+        if (!C.resident) HIP_TRY(launch_reset(C.st, s));
         bool ok = true, again = false;
         for (int l = 0; l < sub && ok; ++l) {
             // p goes straight into y when y is the result and has p's type
@@ -1145,7 +1182,6 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
             }
             LoopOut lo;
             C.pairs = P.pairs && pairs_on(op, tw) && (((uintptr_t)p & 15) == 0);
-            C.chains = P.pairs && op.use_pairs != 0 && chain2d_supported(op, tw);
             C.spare = y_slot ? ws + L.y : nullptr;
             C.spare_bytes = y_slot ? (size_t)n * 8 : 0;
             // (a substep of phi_k, k >= 2, adds to y while it forms its start
@@ -1278,6 +1314,7 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
             };
             LoopOut lo;
             C.chains = P.pairs && op.use_pairs != 0 && chain2d_supported(op, tw);
+            C.resident = C.chains && !P.profile && !P.selector && resident2d_supported(op, tw, P.m_max);
             C.spare = sub == 1 ? ws + L.y : nullptr;   // y_l lives there otherwise
             C.spare_bytes = sub == 1 ? (size_t)n * 8 : 0;
             C.defer = !again;

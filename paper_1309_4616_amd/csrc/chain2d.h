@@ -97,31 +97,6 @@ constexpr int halo_columns(int n, int vec, bool stream) { return stream ? 8 : (n
 // c0 D(x, y) times the Laplacian.
 enum Coef : int { C_CONST = 0, C_FIELD = 1, C_SEP = 2, C_DLAP = 3 };
 
-// The constant-coefficient product at one point, written out in fused
-// operations so that every instantiation rounds it alike (left to the
-// compiler, the diagonal's subtraction is fused in some and not in others,
-// and a call's result would depend on how its products are grouped).
-template <class TC>
-__device__ __forceinline__ TC const_product(TC axm, TC axq, TC aym, TC ayq, TC diag, TC wl, TC wr, TC wm, TC wq, TC wc) {
-#pragma clang fp contract(off)
-    TC u = axm * wl;
-    u = __builtin_elementwise_fma(axq, wr, u);
-    u = __builtin_elementwise_fma(aym, wm, u);
-    u = __builtin_elementwise_fma(ayq, wq, u);
-    return __builtin_elementwise_fma(diag, wc, u);
-}
-// alpha times the face weights on one axis that count in the diagonal
-template <class TC>
-__device__ __forceinline__ TC diag_part(TC af, bool m, bool q) {
-#pragma clang fp contract(off)
-    return (m ? af : (TC)0) + (q ? af : (TC)0);
-}
-template <class TC>
-__device__ __forceinline__ TC minus(TC a, TC b) {
-#pragma clang fp contract(off)
-    return a - b;
-}
-
 // One tile: strip t0, rows [t1 march, (t1+1) march).  s: ||r||^2 (a.first),
 // then ||w||^2, ||p||^2 of each product.  The formulas are those of the pair
 // sweep (constant coefficient) and of the single sweep (the others), term by

@@ -157,6 +157,21 @@ struct ChainShape {
     bool stream;          // streaming stores, strips on whole cache lines
 };
 
+// Arguments of a whole Newton loop in one workgroup (resident2d.hip).
+constexpr int kMaxResidentDegree = 120;   // the coefficients travel as kernel arguments
+struct ResidentArgs {
+    const double* x;      // start vector
+    double* p;            // Newton sum at the stop
+    NewtonState* st;
+    NewtonState* mirror;  // host copy of the state (device address)
+    double afx, afy, afy2;   // alpha c0 / h_d^2, and twice the second
+    double tol;
+    int n[2];
+    int bc, cx, groups, m_max;
+    double d[kMaxResidentDegree + 1];
+    double beta[kMaxResidentDegree];
+};
+
 // The stop tests of several launches at once (sweep.hip): per launch where
 // its partials are and which products it took.
 constexpr int kMaxTestLaunches = 48;
@@ -316,6 +331,10 @@ hipError_t launch_pair_finalize(const double* partials, NewtonState* st, int npa
 bool chain2d_supported(const Op& op, int tw);
 bool chain2d_length(const Op& op, int n);
 hipError_t launch_chain2d(const Op& op, int tw, int n, ChainArgs a, int cus, int* nparts, hipStream_t s);
+// The whole loop in one workgroup (resident2d.hip): degree and stop in the
+// state and its mirror, no finalize.
+bool resident2d_supported(const Op& op, int tw, int m_max);
+hipError_t launch_resident2d(const Op& op, ResidentArgs a, double alpha, hipStream_t s);
 // Bytes of partials a chain sweep of n products writes at most.
 size_t chain2d_partials(const Op& op, int n, int cus);
 size_t pair2d_partials(const Op& op);

@@ -241,6 +241,31 @@ __device__ __forceinline__ TC face_weight(bool exists, bool dir, TC ac, TC anb) 
     return exists ? (TC)0.5 * (ac + anb) : (dir ? ac : (TC)0);
 }
 
+// The 2D constant-coefficient product at one point, written out in fused
+// operations so that every instantiation rounds it alike (left to the
+// compiler, the diagonal's subtraction is fused in some and not in others,
+// and a call's result would depend on how its products are grouped).
+template <class TC>
+__device__ __forceinline__ TC const_product(TC axm, TC axq, TC aym, TC ayq, TC diag, TC wl, TC wr, TC wm, TC wq, TC wc) {
+#pragma clang fp contract(off)
+    TC u = axm * wl;
+    u = __builtin_elementwise_fma(axq, wr, u);
+    u = __builtin_elementwise_fma(aym, wm, u);
+    u = __builtin_elementwise_fma(ayq, wq, u);
+    return __builtin_elementwise_fma(diag, wc, u);
+}
+// alpha times the face weights on one axis that count in the diagonal
+template <class TC>
+__device__ __forceinline__ TC diag_part(TC af, bool m, bool q) {
+#pragma clang fp contract(off)
+    return (m ? af : (TC)0) + (q ? af : (TC)0);
+}
+template <class TC>
+__device__ __forceinline__ TC minus(TC a, TC b) {
+#pragma clang fp contract(off)
+    return a - b;
+}
+
 // Workgroup b runs on XCD b % 8; this maps it to a tile index so that each
 // XCD owns one contiguous run of tiles (neighbouring tiles share its L2).
 __device__ __forceinline__ int xcd_tile(int per_xcd) {

@@ -50,9 +50,12 @@ def make(E, shape, bc, kind, amp=0.4):
     return (lambda: E.StencilOp(shape, h, bc, coef=field)), A
 
 
-# strips: 64 V points less 2 halo columns of 4 to 8 points at inner ends
-SHAPES = [(128, 40), (124, 9), (250, 67), (248, 33), (129, 21), (57, 30), (113, 50), (2, 30), (1, 40), (40, 1),
-          (600, 5), (16, 400), (1000, 37), (300, 300)]
+# strips: 64 V points less 2 halo columns of 4 to 8 points at inner ends; grids
+# of up to 16,384 points run the whole loop in one workgroup (FP64, constant
+# coefficient): rows of one wave (up to 64 or 128 points) and of several
+SHAPES = [(128, 128), (128, 40), (124, 9), (250, 67), (248, 33), (129, 21), (57, 30), (113, 50), (2, 30), (1, 40),
+          (40, 1), (64, 256), (65, 128), (600, 5), (1920, 2), (16, 400), (1000, 37), (300, 300), (113, 301), (64, 257),
+          (130, 140), (57, 300)]
 
 
 @pytest.mark.parametrize("kind", ["const", "field", "separable", "dlap"])
