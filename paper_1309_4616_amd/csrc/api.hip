@@ -1698,6 +1698,7 @@ int expi_op_set_tiles(expi_op* op, int vec, int waves, int march) {
     if (!tiles_valid(o, t)) return fail(EXPI_EINVAL, "tile setting out of range for this operator");
     std::lock_guard<std::mutex> lock(o.mu);
     o.tiles = t;
+    o.tiles_set = true;
     return EXPI_OK;
 }
 
@@ -1775,6 +1776,8 @@ int expi_op_autotune(expi_op* op, int dtype, int reps, void* ws, size_t ws_bytes
     a.j = 1;
     a.guard = 0;
     const Tiles keep = o.tiles;
+    const bool keep_set = o.tiles_set;
+    o.tiles_set = true;
     Tiles best = keep;
     float best_us = 1e30f;
     int nc = 0;
@@ -1863,6 +1866,7 @@ int expi_op_autotune(expi_op* op, int dtype, int reps, void* ws, size_t ws_bytes
     {
         std::lock_guard<std::mutex> lock(o.mu);
         o.tiles = (err == hipSuccess) ? best : keep;
+        o.tiles_set = (err == hipSuccess) || keep_set;
         if (err == hipSuccess) o.use_pairs = use_pairs;
     }
     *n_cand = nc;

@@ -257,6 +257,7 @@ struct Op {
     const double* val;
     int64_t size;
     Tiles tiles;
+    bool tiles_set = false;   // by the caller or the autotuner
     int bdata = 0;        // EXPI_BDATA_* of a 3D Dirichlet stencil
     int bdata_mode = 0;   // EXPI_BDATA_IN_KERNEL or EXPI_BDATA_SEPARATE
     int use_pairs = 1;    // pair sweeps where supported (the autotuner may turn them off)

@@ -322,8 +322,15 @@ Geom make_geom(const Op& op, const Tiles& t) {
 Tiles default_tiles(const Op& op) {
     Tiles t;
     if (op.kind == 2) {
-        t.vec = 4;     // lanes per row (complex entries: 16 bytes each)
-        t.waves = 4;
+        // lanes per row (complex entries: 16 bytes each).  Large matrices with
+        // rows of 24 entries and more take 8 in workgroups of 8 waves: 21
+        // spins, 40 entries per row 474 us against 524-535 us with 4 (19
+        // spins, 28 per row: 80 against 87); small ones 4 (14 spins, 33 per
+        // row: 7.0 against 7.4 us).  Either way the product moves 2.4 GB at
+        // the rate of a large copy; the wider group wastes less of it.
+        const bool wide = op.nrows >= ((int64_t)1 << 16) && op.nnz >= 24 * op.nrows;
+        t.vec = wide ? 8 : 4;
+        t.waves = wide ? 8 : 4;
         t.march = 1;
     } else if (op.kind == 1) {
         t.vec = 8;     // lanes per row
@@ -369,6 +376,12 @@ size_t partials_bytes(const Op& op) {
 hipError_t launch_sweep(const Op& op, int epi, int tin, int tout, SweepArgs a, hipStream_t s,
                         hipEvent_t after_sweep, bool finalize, int* nparts) {
     Tiles t = op.tiles;
+    // FP64 products of larger matrices take 4 lanes per row unless a setting
+    // was chosen: 95 against 108 us at 2^20 rows of 26.5 entries, 10.8 against
+    // 12.8 at 2^16 rows of 9; below 2^15 rows the launch is latency bound and 8
+    // lanes are as good or better (2^12 rows of 33: 7.1 against 8.3 us).
+    // With FP32 vectors the sums round by the lanes' order, so those keep 8.
+    if (op.kind == 1 && !op.tiles_set && tin == 0 && tout == 0 && op.nrows >= (1 << 15)) t.vec = 4;
     if (op.kind == 0 && t.vec == 2) {
         // 16-byte vector accesses need an even row length and aligned arrays
         const bool ok = (op.n[0] % 2 == 0) && aligned16(a.x) && aligned16(a.out) &&
