@@ -89,6 +89,8 @@ struct SweepArgs {
     int ntiles;
     int per_xcd;          // tiles per XCD slot
     int march;            // points marched per thread (stencils)
+    int flat;             // 3D stencils: a tile's waves hold consecutive points of the plane
+    int stream;           // EPI_APPLY: streaming stores
 };
 
 // Arguments of the pair sweep (two Newton products in one pass, pair.hip).
@@ -240,6 +242,7 @@ struct Geom {
     int ntiles;
     int per_xcd;
     int grid;             // workgroups launched (multiple of 8)
+    int flat;             // 3D stencils: rows end to end (SweepArgs::flat)
 };
 
 struct Op {

@@ -19,15 +19,19 @@ constexpr int EPI_START_BD = 7;
 
 namespace tile {
 
-// Dirichlet data f at a boundary node (Sec. III-A): kind 1 z(1-z)xy,
-// kind 2 sin(pi z) exp(-xy).
+// Dirichlet data f at a boundary node (Sec. III-A) are a product
+// Z(z) E(x, y): kind 1 z(1-z) times xy, kind 2 sin(pi z) times exp(-xy).
 template <class TC>
-__device__ __forceinline__ TC boundary_value(int kind, TC x, TC y, TC z) {
-    if (kind == EXPI_BDATA_Z1MZ_XY) return z * ((TC)1 - z) * x * y;
-    if constexpr (std::is_same<TC, float>::value)
-        return sinf(3.14159265358979323846f * z) * expf(-x * y);
-    else
-        return sin(3.14159265358979323846 * z) * exp(-x * y);
+__device__ __forceinline__ TC boundary_z(int kind, TC z) {
+    if (kind == EXPI_BDATA_Z1MZ_XY) return z * ((TC)1 - z);
+    if constexpr (std::is_same<TC, float>::value) return sinf(3.14159265358979323846f * z);
+    else return sin(3.14159265358979323846 * z);
+}
+template <class TC>
+__device__ __forceinline__ TC boundary_xy(int kind, TC x, TC y) {
+    if (kind == EXPI_BDATA_Z1MZ_XY) return x * y;
+    if constexpr (std::is_same<TC, float>::value) return expf(-x * y);
+    else return exp(-x * y);
 }
 
 template <int V, class T, class TC>
@@ -52,6 +56,20 @@ __device__ __forceinline__ void vst(T* __restrict__ p, int idx, const TC (&v)[V]
         *reinterpret_cast<T2*>(p + idx) = t;
     } else {
         p[idx] = (T)v[0];
+    }
+}
+
+// Streaming store: the line need not stay in the caches.
+template <int V, class T, class TC>
+__device__ __forceinline__ void vst_stream(T* __restrict__ p, int idx, const TC (&v)[V]) {
+    if constexpr (V == 2) {
+        typedef T T2 __attribute__((ext_vector_type(2)));
+        T2 t;
+        t.x = (T)v[0];
+        t.y = (T)v[1];
+        __builtin_nontemporal_store(t, reinterpret_cast<T2*>(p + idx));
+    } else {
+        __builtin_nontemporal_store((T)v[0], p + idx);
     }
 }
 
@@ -111,9 +129,22 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
         const int n0 = a.n[0], n1 = a.n[1], n2 = a.n[2];
         const int ns = (DIM == 3) ? n2 : n1;          // marched axis
         const int ss = (DIM == 3) ? n0 * n1 : n0;     // its stride
-        const int i = t0 * (64 * V) + lane * V;
+        int i = t0 * (64 * V) + lane * V;
         int j, kb;
-        if (DIM == 3) {
+        const bool flat = DIM == 3 && a.flat;
+        bool live = true, in_row = true;   // the wave has points; the lane has
+        if (DIM == 3 && flat) {
+            // the waves of the tile hold consecutive points of the plane, rows
+            // end to end (a.flat): the neighbours in x are still those of the
+            // adjacent lanes, and a row's ends are known by their i
+            const int f0 = (t0 * nw + wv) * (64 * V), f = f0 + lane * V, plane = n0 * n1;
+            live = f0 < plane;
+            in_row = f < plane;
+            const int fc = min(f, plane - V);
+            j = fc / n0;
+            i = fc - j * n0;
+            kb = t2 * a.march;
+        } else if (DIM == 3) {
             j = t1 * nw + wv;
             kb = t2 * a.march;
         } else {
@@ -123,8 +154,8 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
         const int ke = min(kb + a.march, ns);
         // whole waves outside the grid skip the march; lanes past the row end
         // stay in it (masked) so that the x-neighbour shuffles see every lane
-        const bool wave_live = (DIM == 2 || j < n1) && kb < ke;
-        const bool active = wave_live && i < n0;
+        const bool wave_live = (flat ? live : (DIM == 2 || j < n1)) && kb < ke;
+        const bool active = wave_live && in_row && i < n0;
         if (wave_live) {
             const bool dir = (a.bc == EXPI_DIRICHLET0);
             const bool ionly = (a.bc == EXPI_INTERIOR_ONLY);
@@ -140,7 +171,7 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
             // the existence flags.  Straight-line loads let the compiler track
             // each one's completion precisely.  Lanes past the row end
             // (i >= n0) load from the last column and store nothing.
-            const int ic = active ? i : (n0 - V);
+            const int ic = (active || flat) ? i : (n0 - V);
             const int jc = (DIM == 3) ? min(j, n1 - 1) : 0;
             const int rowb = ic + ((DIM == 3) ? n0 * jc : 0);       // (i, j) at plane 0
             const int yoffm = (DIM == 3 && eym) ? -n0 : 0;          // y neighbour offsets
@@ -148,8 +179,8 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
             // one extra load per plane feeds the wave-edge lanes: lane 0 its
             // left neighbour, lane 63 its right one, the rest reload a point
             int eoff = 0;
-            if (lane == 0 && ic > 0) eoff = -1;
-            if (lane == 63 && ic + V < n0) eoff = V;
+            if (lane == 0 && (flat ? rowb : ic) > 0) eoff = -1;
+            if (lane == 63 && (flat ? rowb + V < n0 * n1 : ic + V < n0)) eoff = V;
             auto at = [&](int k) { return rowb + ss * min(max(k, 0), ns - 1); };
 
             // separable coefficient: x values of the thread's points and of
@@ -185,6 +216,28 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
 #pragma unroll
                 for (int v = 0; v < V; ++v)
                     Dv[v] = d_coefficient<TC>((TC)((ic + v + poff) * a.hpos[0]), yq);
+            }
+            // boundary data: E at the missing x and y neighbours of the thread's
+            // points (fixed along the march) and at the points themselves; Z of
+            // planes kb .. kb+127 one per lane, read with readlane
+            TC Exm[V], Exq[V], Eym[V], Eyq[V], Exy[V], zb0 = 0, zb1 = 0, Zlo = 0, Zhi = 0;
+            if constexpr (kBD) {
+                const int bk = a.bdata;
+                const TC yp = (TC)((j + 1) * a.hpos[1]);
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const TC xp = (TC)((i + v + 1) * a.hpos[0]);
+                    const bool xm = dir && i + v == 0, xq = dir && i + v == n0 - 1;
+                    Exm[v] = xm ? boundary_xy<TC>(bk, (TC)0, yp) : (TC)0;
+                    Exq[v] = xq ? boundary_xy<TC>(bk, (TC)((n0 + 1) * a.hpos[0]), yp) : (TC)0;
+                    Eym[v] = (dir && !eym) ? boundary_xy<TC>(bk, xp, (TC)0) : (TC)0;
+                    Eyq[v] = (dir && !eyq) ? boundary_xy<TC>(bk, xp, (TC)((n1 + 1) * a.hpos[1])) : (TC)0;
+                    Exy[v] = dir ? boundary_xy<TC>(bk, xp, yp) : (TC)0;
+                }
+                zb0 = boundary_z<TC>(bk, (TC)((kb + lane + 1) * a.hpos[2]));
+                zb1 = boundary_z<TC>(bk, (TC)((kb + 64 + lane + 1) * a.hpos[2]));
+                Zlo = boundary_z<TC>(bk, (TC)0);
+                Zhi = boundary_z<TC>(bk, (TC)((ns + 1) * a.hpos[2]));
             }
             auto zv = [&](int k) -> TC {   // k in [kb-1, kb+126], clamped into the grid
                 const int t = min(k, ns - 1) - (kb - 1);
@@ -261,6 +314,8 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
                             Zq = zv(k + 1);
                         }
                         const bool ezm = k > 0, ezq = k < ns - 1;
+                        TC Zb = 0;
+                        if constexpr (kBD) Zb = k - kb < 64 ? lane_value(zb0, (k - kb) & 63) : lane_value(zb1, (k - kb) & 63);
                         // (3) x neighbours of the outer points from adjacent lanes
                         TC left = 0, right = 0, Fleft = 0, Fright = 0;
                         if (kW) {
@@ -361,27 +416,11 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
                                     }
                                     if constexpr (kBD) {
                                         // a missing neighbour of a boundary-adjacent point
-                                        // is the boundary node, where the data are f
-                                        if (dir && !(exm && exq && eym && eyq && ezm && ezq)) {
-                                            const TC xp = (TC)((iv + 1) * a.hpos[0]);
-                                            const TC yp = (TC)((j + 1) * a.hpos[1]);
-                                            const TC zp = (TC)((k + 1) * a.hpos[2]);
-                                            const int bk = a.bdata;
-                                            TC bt = 0;
-                                            if (!exm) bt += fxm * boundary_value<TC>(bk, (TC)0, yp, zp);
-                                            if (!exq)
-                                                bt += fxq * boundary_value<TC>(
-                                                                bk, (TC)((n0 + 1) * a.hpos[0]), yp, zp);
-                                            if (!eym) bt += fym * boundary_value<TC>(bk, xp, (TC)0, zp);
-                                            if (!eyq)
-                                                bt += fyq * boundary_value<TC>(
-                                                                bk, xp, (TC)((n1 + 1) * a.hpos[1]), zp);
-                                            if (!ezm) bt += fzm * boundary_value<TC>(bk, xp, yp, (TC)0);
-                                            if (!ezq)
-                                                bt += fzq * boundary_value<TC>(
-                                                                bk, xp, yp, (TC)((ns + 1) * a.hpos[2]));
-                                            Aw += bt;
-                                        }
+                                        // is the boundary node, where the data are f = Z E
+                                        // (E is zero at the faces that have a neighbour)
+                                        Aw += Zb * (fxm * Exm[v] + fxq * Exq[v] + fym * Eym[v] + fyq * Eyq[v]);
+                                        if (!ezm) Aw += fzm * (Zlo * Exy[v]);
+                                        if (!ezq) Aw += fzq * (Zhi * Exy[v]);
                                     }
                                     if (kDlap) Aw *= Dp;
                                     if (zero_row) Aw = 0;
@@ -419,7 +458,8 @@ __device__ __forceinline__ void stencil_tile_w(const SweepArgs& a, int t0, int t
                                     }
                                 }
                             }
-                            if (kW) vst<V>(out, idx, wo);
+                            if (kApply && a.stream) vst_stream<V>(out, idx, wo);
+                            else if (kW) vst<V>(out, idx, wo);
                             if (EPI == EPI_NEWTON || EPI == EPI_FIRST) vst<V>(p, idx, po);
                         }
                         idx += ss;

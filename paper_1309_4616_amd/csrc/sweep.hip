@@ -290,6 +290,9 @@ thread_local NewtonState* tl_mirror = nullptr;
 
 void set_state_mirror(NewtonState* mirror) { tl_mirror = mirror; }
 
+// Share of idle lanes (one in kFlatWaste) above which 3D rows go end to end.
+constexpr int kFlatWaste = 16;
+
 Geom make_geom(const Op& op, const Tiles& t) {
     Geom g{};
     g.vec = t.vec;
@@ -300,8 +303,17 @@ Geom make_geom(const Op& op, const Tiles& t) {
         g.tiles[0] = (int)((op.nrows + rows_per - 1) / rows_per);
         g.tiles[1] = g.tiles[2] = 1;
     } else if (op.dim == 3) {
-        g.tiles[0] = (op.n[0] + 64 * t.vec - 1) / (64 * t.vec);
-        g.tiles[1] = (op.n[1] + t.waves - 1) / t.waves;
+        // rows that leave many lanes of their last wave idle go end to end
+        const int wx = 64 * t.vec, per_row = (op.n[0] + wx - 1) / wx;
+        g.flat = kFlatWaste * (per_row * wx - op.n[0]) > per_row * wx;
+        if (g.flat) {
+            const int64_t plane = (int64_t)op.n[0] * op.n[1];
+            g.tiles[0] = (int)((plane + wx * t.waves - 1) / (wx * t.waves));
+            g.tiles[1] = 1;
+        } else {
+            g.tiles[0] = per_row;
+            g.tiles[1] = (op.n[1] + t.waves - 1) / t.waves;
+        }
         g.tiles[2] = (op.n[2] + t.march - 1) / t.march;
     } else {
         const int rows = t.waves * t.march;
@@ -393,6 +405,9 @@ hipError_t launch_sweep(const Op& op, int epi, int tin, int tout, SweepArgs a, h
     a.ntiles = g.ntiles;
     a.per_xcd = g.per_xcd;
     a.march = g.march;
+    a.flat = g.flat;
+    // streaming stores where input and output exceed the last-level cache
+    a.stream = epi == EPI_APPLY && op.kind == 0 && op.size * (tin == 0 ? 16 : 8) > ((int64_t)256 << 20);
     if (nparts) *nparts = g.grid;
     hipError_t e;
     if (op.kind != 0) {
