@@ -404,9 +404,8 @@ int phi_action_noalloc(expi_op *op, int k, double tau, const double *v, double *
  *
  * The work runs in rounds; in each round every unfinished instance takes one
  * step (start vector, Newton products, or the substep update).  A round is
- * three kernels (the tiles of the instances whose step is a start vector,
- * an update or a product that reads the float64 input; the tiles of the
- * other products; then one stop test per instance); nothing inside waits
+ * two kernels (the tiles of every instance's step; then one stop test per
+ * instance); nothing inside waits
  * on memory.  By default a step after the first product forms two Newton
  * products in one pass (expi_batch_set_pairs): w_{j+1} stays in registers,
  * so w_j and p are read and w_{j+2} and p written once for both, and the

@@ -12,10 +12,11 @@
 // The work runs in rounds.  In each round every unfinished instance takes
 // one step of its own sequence (start vector, the first product, two more
 // Newton products, or the update; one product per step when pairs are off).
-// A round is three ordinary kernels:
-//  * two tiles kernels, one for the hot steps (the pairs of products) and
-//    one for the rest: every workgroup builds the same list of unfinished
-//    instances whose step is in its kernel's set and the prefix sums of
+// A round is two ordinary kernels:
+//  * the tiles kernel, whose first half of workgroups takes the hot steps (the
+//    pairs of products) and whose second half the rest: every workgroup builds
+//    the same list of unfinished instances whose step is in its half's set and
+//    the prefix sums of
 //    their tile counts from the states in memory, then works through a
 //    contiguous share of the round's tiles (load balance across uneven
 //    sizes; shares are contiguous per XCD so a tile's neighbours mostly sit
@@ -78,8 +79,8 @@ struct alignas(16) BatchState {  // advanced by the finalize step
 
 struct alignas(64) BatchCtrl {
     unsigned bar_count, bar_gen, abort, rounds;
-    unsigned aux_next;           // round kernels: some instance's next step is an auxiliary one
-    unsigned pad0;
+    unsigned aux[2];             // round kernels, by the round's parity: some instance's step in
+                                 // it is an auxiliary one
     unsigned finished;           // instances done or failed (round kernels)
     unsigned hot_rounds;         // rounds with Newton products on stored vectors
     unsigned pad[8];
@@ -99,6 +100,7 @@ struct BatchArgs {
     void* w1;
     void* p;
     int count, m_max, march, max_rounds, bc;
+    int round;                    // round kernels: index of this round
     int pairs;                    // Newton products two per step where the degree bound allows
     double c0, tol;
     long long deadline_ticks;   // longest wait at a barrier, GPU wall-clock ticks
@@ -757,26 +759,25 @@ __device__ __forceinline__ int find_instance(const int* s_pref, int nact, int t)
 
 // ---- round kernels -----------------------------------------------------------
 
-// The tiles of one round whose steps are in SET.  The grid is a multiple of
-// the XCD count.  The instance list lives in dynamic LDS of
+// The tiles of one round whose steps are in SET, by workgroup `blk` of `nblk`
+// (a multiple of the XCD count).  The instance list lives in dynamic LDS of
 // (2 count + kMaxWaves + 2) ints.
 template <class TW, int SET>
-__global__ __launch_bounds__(kMaxWaves * 64) void batch_tiles_kernel(BatchArgs B) {
+__device__ __forceinline__ void round_tiles(const BatchArgs& B, int blk, int nblk) {
     extern __shared__ int s_dyn[];
     int* s_pref = s_dyn;                  // count + 1
     int* s_ids = s_dyn + B.count + 1;     // count
     int* s_wave = s_ids + B.count;        // kMaxWaves + 1
-    if (B.ctrl->finished >= (unsigned)B.count) return;
-    // the auxiliary kernel of a round without auxiliary steps returns at
-    // once (the flag is set by the previous round's stop tests and cleared
-    // by the hot kernel that follows; kernel boundaries order the three)
+    // the auxiliary part of a round without auxiliary steps returns at once
+    // (the flag is set by the previous round's stop tests and cleared, for
+    // the round after, by the hot part; kernel boundaries order the three)
     constexpr bool kHot = (SET == SET_HOT || SET == SET_PAIR);
-    if (!kHot && B.ctrl->aux_next == 0) return;
+    if (!kHot && B.ctrl->aux[B.round & 1] == 0) return;
     // a round counts when some instance is unfinished at its start (the
     // count changes only in the finalize kernel that ends the round)
-    if (kHot && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (kHot && blk == 0 && threadIdx.x == 0) {
         B.ctrl->rounds += 1;
-        B.ctrl->aux_next = 0;
+        B.ctrl->aux[(B.round + 1) & 1] = 0;
     }
     int nact, total;
     active_list(B, SET, s_pref, s_ids, s_wave, nact, total);
@@ -785,16 +786,17 @@ __global__ __launch_bounds__(kMaxWaves * 64) void batch_tiles_kernel(BatchArgs B
     nact = __builtin_amdgcn_readfirstlane(nact);
     total = __builtin_amdgcn_readfirstlane(total);
     if (nact == 0) return;
-    if (kHot && blockIdx.x == 0 && threadIdx.x == 0) B.ctrl->hot_rounds += 1;
+    if (kHot && blk == 0 && threadIdx.x == 0) B.ctrl->hot_rounds += 1;
     // Grid-stride order over the XCD-major logical wave index: in each pass
     // the waves together take G consecutive tiles and every XCD a contiguous
     // block of them, so tiles that share halo rows and DRAM pages run at the
     // same time on the same L2.  Each wave goes through its tiles alone.
     const int nw = blockDim.x >> 6;
-    const int G = gridDim.x * nw;
+    const int G = nblk * nw;
     // (the same in every lane of a wave: saying so keeps the tile indices,
     // rows and row offsets in scalar registers)
-    const int L = __builtin_amdgcn_readfirstlane(xcd_tile(gridDim.x / kXcd) * nw + (int)(threadIdx.x >> 6));
+    const int first = (blk % kXcd) * (nblk / kXcd) + blk / kXcd;
+    const int L = __builtin_amdgcn_readfirstlane(first * nw + (int)(threadIdx.x >> 6));
     if (L >= total) return;
     int q = __builtin_amdgcn_readfirstlane(find_instance(s_pref, nact, L));
     int inst = __builtin_amdgcn_readfirstlane(s_ids[q]);
@@ -818,6 +820,23 @@ __global__ __launch_bounds__(kMaxWaves * 64) void batch_tiles_kernel(BatchArgs B
     }
 }
 
+// One round's tiles in one launch: the first half of the workgroups take the
+// hot steps (pairs, or single products on stored vectors), the second half
+// the others.  The two sets belong to different instances, so nothing orders
+// them; side by side, the many rounds in which either has few tiles cost one
+// latency instead of two (256 problems, 1490 rounds: 43 + 16 us per round as
+// two kernels).  The first half is dispatched first, so a round with work for
+// the whole device runs as it would as two kernels.
+// (The register bound keeps the occupancy that the pairs have by themselves.)
+template <class TW, bool PAIRS>
+__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(sizeof(TW) == 4 ? 5 : 4))) void
+batch_round_kernel(BatchArgs B) {
+    if (B.ctrl->finished >= (unsigned)B.count) return;
+    const int half = (int)gridDim.x / 2, b = (int)blockIdx.x;
+    if (b < half) round_tiles<TW, PAIRS ? SET_PAIR : SET_HOT>(B, b, half);
+    else round_tiles<TW, PAIRS ? SET_REST : SET_AUX>(B, b - half, half);
+}
+
 size_t tiles_lds_bytes(int count) { return sizeof(int) * (2 * (size_t)count + kMaxWaves + 2); }
 
 // Stop test and state update of one instance per workgroup.
@@ -832,7 +851,7 @@ __global__ __launch_bounds__(256) void batch_finalize_kernel(BatchArgs B) {
         // auxiliary)
         if (next == PH_START || next == PH_UPDATE ||
             (B.pairs && active_phase(next) && next != PH_PAIR))
-            B.ctrl->aux_next = 1;
+            B.ctrl->aux[(B.round + 1) & 1] = 1;
     }
 }
 
@@ -894,7 +913,8 @@ __global__ void batch_reset_kernel(BatchState* st, BatchCtrl* ctrl, int count) {
         ctrl->rounds = 0;
         ctrl->finished = 0;
         ctrl->hot_rounds = 0;
-        ctrl->aux_next = 1;   // the first products read the float64 input
+        ctrl->aux[0] = 1;   // the first products read the float64 input
+        ctrl->aux[1] = 0;
     }
 }
 
@@ -1003,20 +1023,13 @@ BatchArgs make_args(const Batch& b, char* ws, const double* v, double* y) {
     return a;
 }
 
-// The kernel of a round's hot steps (hot = true) or of the others, for the
-// batch's storage type and products per round.
-template <class TW>
-const void* tiles_kernel_t(bool pairs, bool hot) {
-    if (pairs)
-        return hot ? reinterpret_cast<const void*>(batch_tiles_kernel<TW, SET_PAIR>)
-                   : reinterpret_cast<const void*>(batch_tiles_kernel<TW, SET_REST>);
-    return hot ? reinterpret_cast<const void*>(batch_tiles_kernel<TW, SET_HOT>)
-               : reinterpret_cast<const void*>(batch_tiles_kernel<TW, SET_AUX>);
-}
-
-const void* tiles_kernel(const Batch& b, bool hot) {
-    return b.dtype == EXPI_F32 ? tiles_kernel_t<float>(b.pairs != 0, hot)
-                               : tiles_kernel_t<double>(b.pairs != 0, hot);
+// A round's tiles kernel for the batch's storage type and products per round.
+const void* round_kernel(const Batch& b) {
+    if (b.dtype == EXPI_F32)
+        return b.pairs ? reinterpret_cast<const void*>(batch_round_kernel<float, true>)
+                       : reinterpret_cast<const void*>(batch_round_kernel<float, false>);
+    return b.pairs ? reinterpret_cast<const void*>(batch_round_kernel<double, true>)
+                   : reinterpret_cast<const void*>(batch_round_kernel<double, false>);
 }
 
 // The persistent kernel needs every workgroup resident at once.  The grid
@@ -1040,7 +1053,7 @@ int occupancy_grid(Batch& b) {
     // once (occupancy of the hot kernel), a multiple of the XCD count, no
     // more than the batch has tiles
     int per_hot = 0;
-    BHIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_hot, tiles_kernel(b, true), 64 * b.waves,
+    BHIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_hot, round_kernel(b), 64 * b.waves,
                                                       tiles_lds_bytes(b.count)));
     if (per_hot < 1) return bfail(EXPI_EHIP, "batched tiles kernel cannot be resident");
     const int wgs = (b.total_tiles + b.waves - 1) / b.waves;   // a tile per wave
@@ -1068,13 +1081,12 @@ int enqueue(Batch& b, char* ws, const double* v, double* y, hipStream_t s) {
 
 constexpr int kRoundChunk = 8;   // rounds enqueued between status read-backs
 
-// One round: the auxiliary steps, the hot products, then the stop tests.
-hipError_t enqueue_round(const Batch& b, const BatchArgs& a, hipStream_t s) {
-    const size_t lds = tiles_lds_bytes(b.count);
-    void* args[] = {const_cast<BatchArgs*>(&a)};
-    hipError_t e = hipLaunchKernel(tiles_kernel(b, false), dim3(b.round_grid), dim3(64 * b.waves), args, lds, s);
-    if (e == hipSuccess)
-        e = hipLaunchKernel(tiles_kernel(b, true), dim3(b.round_grid), dim3(64 * b.waves), args, lds, s);
+// Round r: the tiles of every unfinished instance, then the stop tests.
+hipError_t enqueue_round(const Batch& b, BatchArgs a, int r, hipStream_t s) {
+    a.round = r;
+    void* args[] = {&a};
+    const hipError_t e = hipLaunchKernel(round_kernel(b), dim3(2 * b.round_grid), dim3(64 * b.waves), args,
+                                         tiles_lds_bytes(b.count), s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(batch_finalize_kernel, dim3(b.count), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -1104,7 +1116,7 @@ int run_rounds(Batch& b, char* ws, const double* v, double* y, hipStream_t s) {
     while (!done) {
         if (enq < b.max_rounds) {
             const int cnt = std::min(kRoundChunk, b.max_rounds - enq);
-            for (int q = 0; q < cnt; ++q) BHIP(enqueue_round(b, a, s));
+            for (int q = 0; q < cnt; ++q) BHIP(enqueue_round(b, a, enq + q, s));
             enq += cnt;
             const int slot = next++ & 3;
             BHIP(hipMemcpyAsync(&b.pinned[slot], a.ctrl, sizeof(BatchCtrl), hipMemcpyDeviceToHost, s));
@@ -1144,23 +1156,21 @@ int build_round_graph(Batch& b, char* ws, const double* v, double* y, int rounds
     k0.kernelParams = p0;
     hipError_t e = hipGraphAddKernelNode(&prev, g, nullptr, 0, &k0);
     void* pa[] = {&a};
-    hipKernelNodeParams kx{};
-    kx.func = const_cast<void*>(tiles_kernel(b, false));
-    kx.gridDim = dim3(b.round_grid);
-    kx.blockDim = dim3(64 * b.waves);
-    kx.sharedMemBytes = (unsigned)tiles_lds_bytes(b.count);
-    kx.kernelParams = pa;
-    hipKernelNodeParams kt = kx;
-    kt.func = const_cast<void*>(tiles_kernel(b, true));
+    hipKernelNodeParams kt{};
+    kt.func = const_cast<void*>(round_kernel(b));
+    kt.gridDim = dim3(2 * b.round_grid);
+    kt.blockDim = dim3(64 * b.waves);
+    kt.sharedMemBytes = (unsigned)tiles_lds_bytes(b.count);
+    kt.kernelParams = pa;
     hipKernelNodeParams kf{};
     kf.func = reinterpret_cast<void*>(batch_finalize_kernel);
     kf.gridDim = dim3(b.count);
     kf.blockDim = dim3(256);
     kf.kernelParams = pa;
     for (int r = 0; r < rounds && e == hipSuccess; ++r) {
-        hipGraphNode_t nx = nullptr, nt = nullptr, nf = nullptr;
-        e = hipGraphAddKernelNode(&nx, g, &prev, 1, &kx);
-        if (e == hipSuccess) e = hipGraphAddKernelNode(&nt, g, &nx, 1, &kt);
+        hipGraphNode_t nt = nullptr, nf = nullptr;
+        a.round = r;   // (a node copies its arguments when it is added)
+        e = hipGraphAddKernelNode(&nt, g, &prev, 1, &kt);
         if (e == hipSuccess) e = hipGraphAddKernelNode(&nf, g, &nt, 1, &kf);
         prev = nf;
     }
