@@ -302,6 +302,27 @@ std::vector<double> get_dd(Op& op, const DdKey& key) {
     return d;
 }
 
+// The complex ones, kept as real parts then imaginary parts.
+void get_dd_skew(Op& op, int k, const DdKey& key, std::vector<double>* re, std::vector<double>* im) {
+    const int count = std::get<4>(key);
+    std::vector<double> d;
+    {
+        std::lock_guard<std::mutex> lock(op.mu);
+        auto it = op.dd_cache.find(key);
+        if (it != op.dd_cache.end()) d = it->second;
+    }
+    if (d.empty()) {
+        d.resize(2 * (size_t)count);
+        divided_differences_skew(k, std::get<1>(key), std::get<2>(key), std::get<3>(key), count, d.data(),
+                                 d.data() + count);
+        std::lock_guard<std::mutex> lock(op.mu);
+        if (op.dd_cache.size() > 64) op.dd_cache.clear();
+        op.dd_cache.emplace(key, d);
+    }
+    re->assign(d.begin(), d.begin() + count);
+    im->assign(d.begin() + count, d.end());
+}
+
 int get_hint(Op& op, const DdKey& key) {
     std::lock_guard<std::mutex> lock(op.mu);
     auto it = op.degree_hint.find(key);
@@ -541,7 +562,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     const int expected = get_hint(*C.op, substep_key(C.key, C.substep));
     const int last_degree = get_hint(*C.op, C.key);
     const int group = (expected >= 2 && (C.chains || !C.pairs)) ? expected : last_degree;
-    const bool defer_on = C.defer && !C.profile && !C.selector && C.di.empty();
+    const bool defer_on = C.defer && !C.profile && !C.selector;
     const bool chain_first = defer_on && C.chains && !start_u && tin == C.tw && C.m_max >= 6;
     int jd = 0;
     bool each = false;   // a test after every deferred launch
@@ -560,13 +581,14 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     TestPlan plan(C);
     int finalized = 0;
     int j = 0;
+    auto mod = [&](int q) { return C.di.empty() ? std::fabs(d[q]) : std::hypot(d[q], C.di[q]); };
     // the tests of the launches collected so far
     auto flush = [&]() -> int {
         if (plan.t.launches == 0) return EXPI_OK;
         int m = plan.t.m0;
         int dof = 0;
-        if (plan.t.roff >= 0) plan.t.d[dof++] = std::fabs(d[0]);
-        for (int q = 0; q < plan.products; ++q) plan.t.d[dof + q] = std::fabs(d[m + q]);
+        if (plan.t.roff >= 0) plan.t.d[dof++] = mod(0);
+        for (int q = 0; q < plan.products; ++q) plan.t.d[dof + q] = mod(m + q);
         plan.t.dfix = d[m + plan.products - 1];
         HIP_TRY(launch_tests(plan.t, C.s));
         finalized += plan.products;
@@ -1419,16 +1441,16 @@ static int run_skew(Op& op, int k, double tau, const double* v, double* y, doubl
         const double delta = tau / sub;
         // the key's k is offset so the real and complex coefficients never share a cache slot
         C.key = DdKey(1000 + k, delta, c, gamma, count);
-        C.d.assign(count, 0.0);
-        C.di.assign(count, 0.0);
-        divided_differences_skew(k, delta, c, gamma, count, C.d.data(), C.di.data());
+        get_dd_skew(op, k, C.key, &C.d, &C.di);
         acc = expi_stats{};
         acc.substeps = sub;
         acc.retries = attempt;
         acc.interval_a = ia;
         acc.interval_b = ib;
         HIP_TRY(launch_reset(C.st, s));
-        bool ok = true;
+        bool ok = true, again = false;
+        C.spare = ws + L.y;   // not used otherwise
+        C.spare_bytes = (size_t)nd * 8;
         for (int l = 0; l < sub && ok; ++l) {
             const bool p_in_y = (sub == 1);
             void* p = p_in_y ? (void*)y : (void*)(ws + L.p);
@@ -1448,8 +1470,18 @@ static int run_skew(Op& op, int k, double tau, const double* v, double* y, doubl
                 src = y;
             }
             LoopOut lo;
+            C.defer = !again;
+            C.substep = l;
+            again = false;
             rc = newton_loop(C, src, 0, p, &lo);
             if (rc) return rc;
+            if (lo.redo) {
+                // the same substep with a stop test per launch
+                if (k == 1 && l > 0) acc.matvecs -= 1;
+                again = true;
+                --l;
+                continue;
+            }
             stats_add(&acc, lo);
             if (lo.done == 2) return fail(EXPI_ENONFINITE, "a norm became inf/NaN (non-finite input?)");
             if (lo.done != 1) {

@@ -144,3 +144,25 @@ def test_hint_on_unstructured_matrix(E):
         yo, so = I.phi_action(A, 1, 60.0 / (b - a), v, 1e-10)
         assert abs(s["degree_last"] - so.degrees[-1]) <= 1
         assert relerr(y.cpu().numpy(), yo) <= TOL_F64
+
+
+def test_hint_on_complex_matrix(E):
+    """The same on a Hermitian operator: e^{-itH}v over substeps whose degree
+    is known, and wrongly known, from earlier calls."""
+    import scipy.sparse as sp
+    g = synth.spin_bath_hamiltonian(9, 3, bath_bonds=10)
+    H = sp.csr_matrix((g.val, g.colind, g.rowptr), shape=(g.n, g.n))
+    op = E.CsrComplexOp(g.n, g.rowptr, g.colind, g.val)
+    _, vec = np.linalg.eigh(H.toarray())
+    inputs = {"eigenvector": vec[:, 0].astype(np.complex128), "rough": synth.complex_uniform_vector(g.n, 2)}
+    for k in (0, 1):
+        for name in ("rough", "rough", "eigenvector", "rough", "eigenvector", "eigenvector"):
+            print(f"hint complex k={k} {name}", flush=True)
+            y, s = E.skew_phi_action(op, k, 9.0, T(inputs[name]), tol=1e-10)
+            fresh = E.CsrComplexOp(g.n, g.rowptr, g.colind, g.val)
+            z, r = E.skew_phi_action(fresh, k, 9.0, T(inputs[name]), tol=1e-10)
+            assert s["matvecs"] == r["matvecs"] and s["degree_last"] == r["degree_last"]
+            # single products either way: the same bits
+            assert np.array_equal(y.cpu().numpy(), z.cpu().numpy()), (k, name)
+            yo, _ = I.skew_phi_action(H, k, 9.0, inputs[name], 1e-10)
+            assert relerr(y.cpu().numpy(), yo) <= TOL_F64, (k, name)
