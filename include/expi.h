@@ -127,7 +127,8 @@ typedef struct {
     int32_t timed_pairs;    /* pair sweeps among the timed launches (each covers
                                two products; timed_products counts both)       */
     double  pair_ms;        /* summed device time of those pair sweeps          */
-    int32_t pair_launches;  /* pair sweeps that did work (began before the stop) */
+    int32_t pair_launches;  /* pair sweeps that did work (began before the stop);
+                               a launch of more products counts them two by two */
     int32_t single_launches;/* single-product sweeps that did work              */
     int32_t fused_starts;   /* start vectors formed inside a pair sweep         */
     int32_t reserved3;
@@ -163,7 +164,11 @@ typedef struct {
      * boundary handling), consecutive products run
      * as pair sweeps that keep w_{j+1} on chip (same arithmetic, half the
      * vector traffic) and test the stop rule after each of the two (unless
-     * the operator's pair setting, expi_op_set_pairs, is 0). */
+     * the operator's pair setting, expi_op_set_pairs, is 0).  2D stencils
+     * take up to six products per pass, or the whole loop in one launch on
+     * small grids, where that gives the same results (FP64; other than
+     * constant coefficients also with FP32 storage); not with `profile`,
+     * which times launch by launch, nor with a selector. */
     int32_t no_pairs;
     /* Exponential Euler steps: the start-vector sweep r = A u + u - u^3 of
      * the first substep can run as the first half of a pair sweep whose
@@ -257,6 +262,8 @@ int expi_op_get_tiles(const expi_op *op, int *vec, int *waves, int *march);
  * use = 4..64 (a multiple of 4) takes them with tiles of that many grid
  * rows (with 1 the height follows the grid size: 16 rows, fewer where the
  * grid has too few tiles for the device).  EXPI_EINVAL for other values.
+ * 0 also turns off the passes of more than two products on 2D stencils of
+ * any coefficient kind.
  * expi_op_get_pairs returns the stored value (0, 1 or a row count). */
 int expi_op_set_pairs(expi_op *op, int use);
 int expi_op_get_pairs(const expi_op *op, int *use);

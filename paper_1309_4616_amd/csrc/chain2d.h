@@ -27,9 +27,9 @@
 // tile, and costs no exchange, no LDS and no barrier.
 //
 // The march is unrolled six rows per block and every queue is indexed by row
-// modulo 6, so the queues rotate by renaming: rows s+1 and s+2 of w_j load
-// straight into slots that rows s-5 and s-4 have left.  (With the rows ahead
-// in two registers of their own, copied into the queue when their turn came,
+// modulo 6, so the queues rotate by renaming: rows s+1 to s+3 of w_j load
+// straight into slots that rows s-5 to s-3 have left.  (With the rows ahead
+// in registers of their own, copied into the queue when their turn came,
 // the compiler moved them at the loop's end and the wave waited there for
 // every load in flight: 516 us per pass at 8192^2, T = 6.)  A tile starts
 // with 2T steps that only fill the levels, each from its first valid row on.
