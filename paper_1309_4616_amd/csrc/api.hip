@@ -343,6 +343,32 @@ void set_hint(Op& op, const DdKey& key, int m) {
     op.degree_hint[key] = m;
 }
 
+// The lowest degree seen lately.  Tests are deferred no further than that: a
+// loop that stops before them is run again launch by launch, about twice its
+// work, so inputs whose degree goes up and down must not cause it each time.
+// With degrees in random order a loop is lower than all of the last 16 or more
+// at most once in 17; the tested launches between the lowest and the usual
+// degree cost one stop test each.
+constexpr int kDegreeWindow = 16;
+
+int get_low(Op& op, const DdKey& key) {
+    std::lock_guard<std::mutex> lock(op.mu);
+    auto it = op.degree_low.find(key);
+    return it == op.degree_low.end() ? 0 : it->second.low;
+}
+
+void set_low(Op& op, const DdKey& key, int m) {
+    std::lock_guard<std::mutex> lock(op.mu);
+    if (op.degree_low.size() > 1024) op.degree_low.clear();
+    DegreeWindow& w = op.degree_low[key];
+    w.low = w.low ? std::min(w.low, m) : m;
+    w.next = w.count ? std::min(w.next, m) : m;
+    if (++w.count >= kDegreeWindow) {
+        w.low = w.next;
+        w.count = 0;
+    }
+}
+
 // ---- one Newton loop -----------------------------------------------------------
 struct LoopOut {
     int m = 0;
@@ -553,15 +579,17 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     // without a test each (their norms are kept) and are tested together:
     // jd is where the tested launches begin.  Without one, only chains of
     // products are tested together, up to half the estimated degree.
-    // expected: the degree this substep stopped at last time.  group: the
-    // degree the launches are laid out for.  A stop at the first product of a
+    // expected: the lowest degree this substep stopped at lately; no test at
+    // or past it is deferred.  group: the degree the launches are laid out
+    // for, that of the last time.  A stop at the first product of a
     // pair leaves a rounding of the extra term in p, and pairs and single
     // products sum their norms in different orders, so 3D pairs are laid out
     // for the degree of the last loop of this length, whichever substep it
     // was, and only their tests are deferred.
-    const int expected = get_hint(*C.op, substep_key(C.key, C.substep));
+    const int expected = get_low(*C.op, substep_key(C.key, C.substep));
+    const int own_degree = get_hint(*C.op, substep_key(C.key, C.substep));
     const int last_degree = get_hint(*C.op, C.key);
-    const int group = (expected >= 2 && (C.chains || !C.pairs)) ? expected : last_degree;
+    const int group = (own_degree >= 2 && (C.chains || !C.pairs)) ? own_degree : last_degree;
     const bool defer_on = C.defer && !C.profile && !C.selector;
     const bool chain_first = defer_on && C.chains && !start_u && tin == C.tw && C.m_max >= 6;
     int jd = 0;
@@ -1006,6 +1034,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     if (last.done == 1) {
         set_hint(*C.op, C.key, last.m);
         set_hint(*C.op, substep_key(C.key, C.substep), last.m);
+        set_low(*C.op, substep_key(C.key, C.substep), last.m);
     }
     if (last.done != 2) {
         // launches that began before the stop did work (the opening ones
