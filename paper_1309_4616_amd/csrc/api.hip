@@ -470,6 +470,8 @@ struct TestPlan {
 
 // Bytes of partials a single product writes at most (one point per lane).
 size_t single_partials(const Op& op) {
+    // (the settings launch_sweep takes by itself for matrices have no larger
+    // grid: 4 lanes per row, or two waves where the grid is at its limit)
     Tiles t = op.tiles;
     if (op.kind == 0) t.vec = 1;
     return (size_t)make_geom(op, t).grid * 4 * sizeof(double);
