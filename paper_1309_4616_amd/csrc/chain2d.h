@@ -8,7 +8,7 @@
 // written once: 32 B per point (FP64) for T products.
 //
 // What bounds it: HBM beyond the last-level cache.  At 8192^2 FP64 a pass
-// takes 485 us with six products and 420 us with two (2.2 GB each way), so
+// of six products takes 464 us and moves 2.2 GB, a pair sweep 424 us, so
 // phi_1 of degree 25 takes 2.3 ms against 5.5 ms in pairs.  The arithmetic
 // (25 FP64 instructions per point and product, about 200 us for six) hides
 // behind the memory time at one or two waves per SIMD alike; a seventh level

@@ -338,8 +338,9 @@ Tiles default_tiles(const Op& op) {
         // rows of 24 entries and more take 8 in workgroups of 8 waves: 21
         // spins, 40 entries per row 474 us against 524-535 us with 4 (19
         // spins, 28 per row: 80 against 87); small ones 4 (14 spins, 33 per
-        // row: 7.0 against 7.4 us; 17 spins: no difference).  Either way the product moves 2.4 GB at
-        // the rate of a large copy; the wider group wastes less of it.
+        // row: 7.0 against 7.4 us; 17 spins: no difference).  At 21 spins the
+        // product moves 2.6 GB at the rate of a large copy; the wider group
+        // wastes less of it.
         const bool wide = op.nrows >= ((int64_t)1 << 18) && op.nnz >= 24 * op.nrows;
         t.vec = wide ? 8 : 4;
         t.waves = wide ? 8 : 4;
