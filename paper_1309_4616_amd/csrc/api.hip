@@ -436,8 +436,9 @@ struct TestPlan {
     TestArgs t{};
     const Ctx& C;
     size_t used = 0, used_spare = 0, cap;
+    size_t room;           // the larger of the two: what one launch may take
     int products = 0;
-    explicit TestPlan(const Ctx& c) : C(c), cap(partials_bytes(*c.op)) {
+    explicit TestPlan(const Ctx& c) : C(c), cap(partials_bytes(*c.op)), room(std::max(cap, c.spare_bytes)) {
         t.st = c.st;
         t.tol = c.tol;
         t.roff = -1;
@@ -631,7 +632,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     // products j .. j+n-1 as one chain (j = 0: from the start vector), tested
     // by the next flush; false in *ok when its partials have no place
     auto chain = [&](int j, int n, bool* ok) -> int {
-        double* part = plan.place(chain2d_partials(*C.op, n, device_cus()), n);
+        double* part = plan.place(chain2d_partials(*C.op, n, device_cus(), plan.room), n);
         *ok = part != nullptr;
         if (!part) return EXPI_OK;
         if (plan.t.launches == 0) plan.t.m0 = j + 1;
@@ -650,7 +651,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         }
         b.guard = plan.t.cont;
         int np = 0;
-        HIP_TRY(launch_chain2d(*C.op, C.tw, n, b, device_cus(), &np, C.s));
+        HIP_TRY(launch_chain2d(*C.op, C.tw, n, b, device_cus(), plan.room, &np, C.s));
         if (b.first) plan.t.roff = 0;
         else cur ^= 1;
         plan.add(part, np, 16, 1, n);
@@ -894,6 +895,9 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         if (rc) return rc;
         j += two ? 2 : 1;
     }
+    // (an empty plan has room for any launch, so a chain that opens the loop
+    // has run: the launches below go on from it)
+    if (j == 0) return fail(EXPI_EHIP, "internal: the opening chain was not launched");
     {
         const int rc = flush();
         if (rc) return rc;

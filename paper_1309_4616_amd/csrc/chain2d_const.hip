@@ -44,8 +44,12 @@ bool chain2d_length(const Op& op, int n) {
     return op.coef == EXPI_COEF_CONST ? (n == 2 || (n >= 4 && n <= 6)) : (n == 2 || n == 4);
 }
 
-static ChainShape chain2d_shape(const Op& op, int n, int cus, bool aligned) {
+// room: bytes the launch has for its partials; the grid is no larger than they
+// hold (the waves stride over the tiles).  partials_bytes always has room for
+// 256 workgroups, one wave per SIMD.
+static ChainShape chain2d_shape(const Op& op, int n, int cus, bool aligned, size_t room) {
     ChainShape g{};
+    const int fit = (int)std::min<size_t>(room / (chain::kStride * sizeof(double)), 1 << 20) / kXcd * kXcd;
     g.vec = (op.n[0] % 2 == 0 && aligned) ? 2 : 1;
     // streaming stores where the three vectors of a pass exceed the last-level
     // cache (256 MB): at 8192^2 they leave it to the rows read twice, 516 ->
@@ -58,25 +62,26 @@ static ChainShape chain2d_shape(const Op& op, int n, int cus, bool aligned) {
     // once, so that every wave takes one tile and the rows loaded twice are
     // few; a multiple of the unrolled block
     const int u = chain::kRows;
-    const int slots = 2 * 4 * std::max(cus, kXcd);
+    const int slots = std::min(2 * 4 * std::max(cus, kXcd), chain::kWaves * fit);
     const int bands = std::max(1, slots / g.tiles0);
     int march = (op.n[1] + bands - 1) / bands;
     march = (march + u - 1) / u * u;
     g.march = march;
     g.ntiles = g.tiles0 * ((op.n[1] + march - 1) / march);
     const int wgs = (g.ntiles + chain::kWaves - 1) / chain::kWaves;
-    const int most = 2 * std::max(cus, kXcd) / kXcd * kXcd;
+    const int most = std::min(2 * std::max(cus, kXcd) / kXcd * kXcd, fit);
     g.grid = std::min(most, (wgs + kXcd - 1) / kXcd * kXcd);
     return g;
 }
 
-size_t chain2d_partials(const Op& op, int n, int cus) {
+size_t chain2d_partials(const Op& op, int n, int cus, size_t room) {
     // whatever the points per lane turn out to be
-    const int grid = std::max(chain2d_shape(op, n, cus, false).grid, chain2d_shape(op, n, cus, true).grid);
+    const int grid = std::max(chain2d_shape(op, n, cus, false, room).grid, chain2d_shape(op, n, cus, true, room).grid);
     return (size_t)grid * chain::kStride * sizeof(double);
 }
 
-hipError_t launch_chain2d(const Op& op, int tw, int n, ChainArgs a, int cus, int* nparts, hipStream_t s) {
+hipError_t launch_chain2d(const Op& op, int tw, int n, ChainArgs a, int cus, size_t room, int* nparts,
+                          hipStream_t s) {
     if (!chain2d_supported(op, tw) || !chain2d_length(op, n)) return hipErrorInvalidValue;
     for (int q = 0; q < 2; ++q) {
         a.n[q] = op.n[q];
@@ -95,7 +100,8 @@ hipError_t launch_chain2d(const Op& op, int tw, int n, ChainArgs a, int cus, int
         return (uintptr_t)a.x % al == 0 && (uintptr_t)a.out % al == 0 && (uintptr_t)a.p % al == 0;
     };
     const bool fld = op.coef != EXPI_COEF_FIELD || (uintptr_t)op.field % 16 == 0;
-    const ChainShape g = chain2d_shape(op, n, cus, on(2 * sz) && fld);
+    const ChainShape g = chain2d_shape(op, n, cus, on(2 * sz) && fld, room);
+    if (g.grid < kXcd) return hipErrorInvalidValue;
     a.march = g.march;
     a.tiles0 = g.tiles0;
     a.ntiles = g.ntiles;

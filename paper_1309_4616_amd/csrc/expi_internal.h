@@ -339,16 +339,19 @@ hipError_t launch_pair_finalize(const double* partials, NewtonState* st, int npa
                                 int guard, double d0, double d1, double d2, double tol, int mode,
                                 int outbuf, hipStream_t s);
 // Chain sweeps of 2D stencils (chain2d.h): n products from a.x, partials of
-// *nparts workgroups (16 doubles each) at a.partials, no finalize.
+// *nparts workgroups (16 doubles each, `room` bytes at most) at a.partials, no
+// finalize.
 bool chain2d_supported(const Op& op, int tw);
 bool chain2d_length(const Op& op, int n);
-hipError_t launch_chain2d(const Op& op, int tw, int n, ChainArgs a, int cus, int* nparts, hipStream_t s);
+hipError_t launch_chain2d(const Op& op, int tw, int n, ChainArgs a, int cus, size_t room, int* nparts,
+                          hipStream_t s);
 // The whole loop in one workgroup (resident2d.hip): degree and stop in the
 // state and its mirror, no finalize.
 bool resident2d_supported(const Op& op, int tw, int m_max);
 hipError_t launch_resident2d(const Op& op, ResidentArgs a, double alpha, hipStream_t s);
-// Bytes of partials a chain sweep of n products writes at most.
-size_t chain2d_partials(const Op& op, int n, int cus);
+// Bytes of partials a chain sweep of n products writes at most (no more than
+// `room`, which partials_bytes always is enough for).
+size_t chain2d_partials(const Op& op, int n, int cus, size_t room);
 size_t pair2d_partials(const Op& op);
 // The stop tests of the launches in `t`, in order of their products: the
 // state as the finalize kernels of the launches would have left it.  A stop
