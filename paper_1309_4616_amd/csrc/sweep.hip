@@ -89,6 +89,7 @@ __device__ void finalize_tests(const FinalArgs& f) {
     st->pnorm = pn;
     st->wnorm = wn;
     st->m = m;
+    st->fix = 0.0;   // (an earlier substep may have left one)
     st->done = done;
     if (EPI == EPI_FIRST) {
         st->rnorm = sqrt(s0);
