@@ -293,6 +293,8 @@ __global__ __launch_bounds__(kResWaves * 64, 1) void resident2d_loop(ResidentArg
             s->err = err;
             s->pnorm = pn;
             s->wnorm = wn;
+            // (the record is not cleared before: no term of an earlier loop)
+            for (int q = m + 1; q < kHist; ++q) s->hist[q] = 0.0;
             s->done = done;
         }
     }

@@ -214,7 +214,6 @@ __global__ __launch_bounds__(kTestThreads) void tests_kernel(TestArgs f) {
         if (q > 0) tprev = ts[q - 1];
         else if (lead) tprev = f.d[0] * sqrt(sum[0]);
         const int m = f.m0 + q;
-        if (m < kHist) st->hist[m] = ts[q];   // (terms past a stop are not looked at)
         if (!isfinite(wns[q]) || !isfinite(pns[q]) || !isfinite(tprev)) done = 2;
         else if (m >= 2 && tprev + ts[q] <= f.tol * pns[q]) done = 1;
         if (done) atomicMin(&first_stop, q);
@@ -222,6 +221,8 @@ __global__ __launch_bounds__(kTestThreads) void tests_kernel(TestArgs f) {
     __syncthreads();
     const int stop = min(first_stop, total - 1);
     if (q != stop) return;
+    // (no term past the stop; f.m0 is 0 or 1 in a loop's first tests)
+    for (int u = 0; u <= q && f.m0 + u < kHist; ++u) st->hist[f.m0 + u] = ts[u];
     if (lead) {
         st->rnorm = sqrt(sum[0]);
         st->hist[0] = f.d[0] * sqrt(sum[0]);

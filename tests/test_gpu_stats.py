@@ -1,0 +1,58 @@
+"""What a call reports does not depend on what the operator or the workspace
+saw before: the first terms and the counts of a call with a known degree
+against a fresh operator's launch by launch (params.profile).
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1309_4616_amd as E
+    return E
+
+
+def T(a):
+    import torch
+    return torch.as_tensor(np.ascontiguousarray(a), device="cuda:0")
+
+
+def make(E, name):
+    """(new operator, points)"""
+    if name == "csr":
+        g = synth.rgg_negative_laplacian(3000, 1, 12.0)
+        return (lambda: E.CsrOp(g.n, g.rowptr, g.colind, g.val)), g.n
+    shape = {"resident": (100, 100), "const2d": (300, 300), "field2d": (140, 90), "const3d": (128, 12, 10),
+             "field3d": (40, 20, 9)}[name]
+    h = tuple(1.0 / n for n in shape)
+    n = int(np.prod(shape))
+    coef = 1.0 + 0.3 * synth.uniform_vector(n, 3) if name.startswith("field") else 1.0
+    return (lambda: E.StencilOp(shape, h, "neumann0", coef=coef)), n
+
+
+@pytest.mark.parametrize("name", ["resident", "const2d", "field2d", "const3d", "field3d", "csr"])
+def test_first_terms_are_this_calls_own(E, name):
+    """A constant vector stops at degree 2 under zero-flux boundaries: no
+    third term, whatever earlier calls (enough of them to use every read-back
+    slot) and the products past the stop had."""
+    new, n = make(E, name)
+    op = new()
+    a, b = op.interval()
+    tau = 13.0 / (b - a)
+    rough, ones = T(synth.uniform_vector(n, 1)), T(np.ones(n))
+    for _ in range(66):
+        E.phi_action(op, 1, tau, rough, tol=1e-10)
+    _, s = E.phi_action(op, 1, tau, ones, tol=1e-10)
+    _, r = E.phi_action(new(), 1, tau, ones, tol=1e-10, params=E.LejaParams(profile=True))
+    print(name, s["t_first"], r["t_first"], s["degree_last"], flush=True)
+    assert s["degree_last"] == r["degree_last"] == 2
+    scale = r["t_first"][0]
+    assert np.allclose(s["t_first"], r["t_first"], rtol=1e-12, atol=1e-12 * scale)
+    assert s["t_first"][3:] == [0.0, 0.0]
