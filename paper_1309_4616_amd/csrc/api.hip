@@ -622,7 +622,8 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         for (int q = 0; q < plan.products; ++q) plan.t.d[dof + q] = mod(m + q);
         plan.t.dfix = d[m + plan.products - 1];
         HIP_TRY(launch_tests(plan.t, C.s));
-        finalized += plan.products;
+        // (the first value of a fused start is the start vector's norm)
+        finalized += plan.products - (m == 0 ? 1 : 0);
         plan.t.m0 = m + plan.products;
         plan.t.roff = -1;
         plan.t.cont = 1;

@@ -56,3 +56,22 @@ def test_first_terms_are_this_calls_own(E, name):
     scale = r["t_first"][0]
     assert np.allclose(s["t_first"], r["t_first"], rtol=1e-12, atol=1e-12 * scale)
     assert s["t_first"][3:] == [0.0, 0.0]
+
+
+@pytest.mark.parametrize("fuse", [1, 2])
+def test_tested_products_are_counted_alike(E, fuse):
+    """An Euler step counts the products whose norms were reduced, not the
+    norm of its start vector, whether the start vector is formed inside the
+    first pair sweep (2) or not (1), tested launch by launch or afterwards."""
+    new, n = make(E, "const3d")
+    op = new()
+    a, b = op.interval()
+    tau = 13.0 / (b - a)
+    u0 = 0.5 + 0.1 * synth.uniform_vector(n, 2)
+    step = lambda o, **kw: E.expeuler_step(o, tau, T(u0), tol=1e-10, params=E.LejaParams(fuse_start=fuse, **kw))
+    ref = new()
+    for call in range(8):
+        s, r = step(op), step(ref, profile=True)
+        print(f"finalized {s['finalized']} of degree {s['degree_last']} (launch by launch {r['finalized']})", flush=True)
+        assert s["fused_starts"] == fuse - 1 and s["degree_last"] == r["degree_last"]
+        assert s["finalized"] == r["finalized"], call
