@@ -249,7 +249,10 @@ int64_t expi_op_size(const expi_op *op);
  * march = points each thread marches along the slowest axis (4..120, a
  * multiple of 4).
  * CSR: vec = lanes per row (4, 8 or 16), waves (1..8), march = 1.
- * EXPI_EINVAL for anything else.  The workspace size does not depend on it. */
+ * EXPI_EINVAL for anything else.  The workspace size does not depend on it.
+ * expi_op_get_tiles reports the setting in use; for a CSR operator that was
+ * given none, that of FP64 calls, which follows the row count (FP32 calls then
+ * run with 8 lanes and 4 waves). */
 int expi_op_set_tiles(expi_op *op, int vec, int waves, int march);
 int expi_op_get_tiles(const expi_op *op, int *vec, int *waves, int *march);
 

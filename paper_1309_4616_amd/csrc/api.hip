@@ -469,11 +469,10 @@ struct TestPlan {
     }
 };
 
-// Bytes of partials a single product writes at most (one point per lane).
-size_t single_partials(const Op& op) {
-    // (the settings launch_sweep takes by itself for matrices have no larger
-    // grid: 4 lanes per row, or two waves where the grid is at its limit)
-    Tiles t = op.tiles;
+// Bytes of partials a single product into vectors of storage code tw writes at
+// most (one point per lane).
+size_t single_partials(const Op& op, int tw) {
+    Tiles t = product_tiles(op, tw, tw);
     if (op.kind == 0) t.vec = 1;
     return (size_t)make_geom(op, t).grid * 4 * sizeof(double);
 }
@@ -678,7 +677,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         bool fin0 = true;
         if (jd > 2) {
             // the opening launch joins the deferred tests
-            part0 = plan.place(!(start_u || first_pair) ? single_partials(*C.op)
+            part0 = plan.place(!(start_u || first_pair) ? single_partials(*C.op, C.tw)
                                : C.op->dim == 2         ? pair2d_partials(*C.op)
                                                         : (size_t)pair_geom(*C.op, device_cus()).grid * 64,
                                2);
@@ -882,7 +881,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         }
         if (each) break;
         const bool two = C.pairs && left >= 2;
-        const size_t bytes = !two ? single_partials(*C.op)
+        const size_t bytes = !two ? single_partials(*C.op, C.tw)
                              : C.op->dim == 2 ? pair2d_partials(*C.op)
                                               : (size_t)pair_geom(*C.op, device_cus()).grid * 32;
         double* part = plan.place(bytes, two ? 2 : 1);

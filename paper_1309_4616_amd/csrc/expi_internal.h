@@ -290,6 +290,8 @@ constexpr int kCsrGrid = 2048;   // workgroups of a CSR sweep at most (grid-stri
 
 Geom make_geom(const Op& op, const Tiles& t);
 Tiles default_tiles(const Op& op);
+// The setting a product between vectors of these storage codes runs with.
+Tiles product_tiles(const Op& op, int tin, int tout);
 bool tiles_valid(const Op& op, const Tiles& t);
 size_t partials_bytes(const Op& op);
 

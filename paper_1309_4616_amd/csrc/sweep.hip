@@ -333,6 +333,9 @@ Geom make_geom(const Op& op, const Tiles& t) {
     return g;
 }
 
+// CSR products of small matrices, and of all with FP32 vectors: 8 lanes per row.
+constexpr Tiles kCsrTiles{8, 4, 1};
+
 Tiles default_tiles(const Op& op) {
     Tiles t;
     if (op.kind == 2) {
@@ -348,9 +351,25 @@ Tiles default_tiles(const Op& op) {
         t.waves = wide ? 8 : 4;
         t.march = 1;
     } else if (op.kind == 1) {
-        t.vec = 8;     // lanes per row
-        t.waves = 4;
-        t.march = 1;
+        // lanes per row, for FP64 vectors (product_tiles has FP32's).  Larger
+        // matrices take 4: 95 against 108 us at 2^20 rows of 26.5 entries,
+        // 11.8 against 13.9 at 2^16; below 2^15 rows the launch is latency
+        // bound and 8 lanes are as good or better (2^12 rows of 33: 7.1
+        // against 8.3 us).  The grid strides over kCsrPass rows at 4 lanes, so
+        // a last pass that is mostly empty costs a whole one: there (more than
+        // 1.2 passes' time per pass of rows) 8 lanes in workgroups of two
+        // waves are faster, 20.5 against 25.4 us at 161,468 rows and 30.4
+        // against 32.5 at 300,000 (8 lanes of four waves: 23.5 and 32.2); at
+        // 370,000 they take 34.3, 4 lanes 33.3.
+        t = kCsrTiles;
+        if (op.nrows >= (1 << 15)) {
+            constexpr int64_t kCsrPass = kCsrGrid * 64;
+            const int64_t passes = (op.nrows + kCsrPass - 1) / kCsrPass;
+            if (op.nrows < kCsrPass || (op.nrows > kCsrPass && 5 * passes * kCsrPass <= 6 * op.nrows))
+                t.vec = 4;
+            else
+                t.waves = 2;
+        }
     } else {
         // measured best at 256^3 (fused Newton product, FP64 and FP32)
         t.vec = 2;
@@ -358,6 +377,13 @@ Tiles default_tiles(const Op& op) {
         t.march = (op.dim == 3) ? 32 : 8;
     }
     return t;
+}
+
+// With FP32 vectors a CSR product's sums round by the lanes' order, so those
+// keep 8 lanes until a setting is chosen.
+Tiles product_tiles(const Op& op, int tin, int tout) {
+    if (op.kind == 1 && !op.tiles_set && (tin != 0 || tout != 0)) return kCsrTiles;
+    return op.tiles;
 }
 
 bool tiles_valid(const Op& op, const Tiles& t) {
@@ -390,25 +416,7 @@ size_t partials_bytes(const Op& op) {
 
 hipError_t launch_sweep(const Op& op, int epi, int tin, int tout, SweepArgs a, hipStream_t s,
                         hipEvent_t after_sweep, bool finalize, int* nparts) {
-    Tiles t = op.tiles;
-    // FP64 products of larger matrices take 4 lanes per row unless a setting
-    // was chosen: 95 against 108 us at 2^20 rows of 26.5 entries, 11.8 against
-    // 13.9 at 2^16; below 2^15 rows the launch is latency bound and 8 lanes
-    // are as good or better (2^12 rows of 33: 7.1 against 8.3 us).  The grid
-    // strides over kCsrPass rows at 4 lanes, so a last pass that is mostly
-    // empty costs a whole one: there (more than 1.2 passes' time per pass of
-    // rows) 8 lanes in workgroups of two waves are faster, 20.5 against 25.4
-    // us at 161,468 rows and 30.4 against 32.5 at 300,000 (8 lanes of four
-    // waves: 23.5 and 32.2); at 370,000 they take 34.3, 4 lanes 33.3.
-    // With FP32 vectors the sums round by the lanes' order, so those keep 8.
-    if (op.kind == 1 && !op.tiles_set && tin == 0 && tout == 0 && op.nrows >= (1 << 15)) {
-        constexpr int64_t kCsrPass = kCsrGrid * 64;
-        const int64_t passes = (op.nrows + kCsrPass - 1) / kCsrPass;
-        if (op.nrows < kCsrPass || (op.nrows > kCsrPass && 5 * passes * kCsrPass <= 6 * op.nrows))
-            t.vec = 4;
-        else
-            t.waves = 2;
-    }
+    Tiles t = product_tiles(op, tin, tout);
     if (op.kind == 0 && t.vec == 2) {
         // 16-byte vector accesses need an even row length and aligned arrays
         const bool ok = (op.n[0] % 2 == 0) && aligned16(a.x) && aligned16(a.out) &&
