@@ -360,15 +360,18 @@ Tiles default_tiles(const Op& op) {
         // 1.2 passes' time per pass of rows) 8 lanes in workgroups of two
         // waves are faster, 20.5 against 25.4 us at 161,468 rows and 30.4
         // against 32.5 at 300,000 (8 lanes of four waves: 23.5 and 32.2); at
-        // 370,000 they take 34.3, 4 lanes 33.3.
+        // 370,000 they take 34.3, 4 lanes 33.3.  So they are where a single
+        // pass is more than three quarters full and every workgroup has its
+        // rows at once (phi_1 of degree 39, rows of 26 entries: 253 against
+        // 275 us per call at 100,000 rows, 300 against 342 at 131,072; 241
+        // against 236 at 80,000).
         t = kCsrTiles;
         if (op.nrows >= (1 << 15)) {
             constexpr int64_t kCsrPass = kCsrGrid * 64;
             const int64_t passes = (op.nrows + kCsrPass - 1) / kCsrPass;
-            if (op.nrows < kCsrPass || (op.nrows > kCsrPass && 5 * passes * kCsrPass <= 6 * op.nrows))
-                t.vec = 4;
-            else
-                t.waves = 2;
+            const bool two_waves = passes == 1 ? 4 * op.nrows > 3 * kCsrPass : 5 * passes * kCsrPass > 6 * op.nrows;
+            if (two_waves) t.waves = 2;
+            else t.vec = 4;
         }
     } else {
         // measured best at 256^3 (fused Newton product, FP64 and FP32)

@@ -27,8 +27,8 @@ def setting(L, n, new=None):
     return v.value, w.value, m.value
 
 
-@pytest.mark.parametrize("n,want", [(2**15 - 1, (8, 4, 1)), (2**15, (4, 4, 1)), (2**17 - 1, (4, 4, 1)),
-                                    (2**17 + 1, (8, 2, 1)), (161468, (8, 2, 1)), (218453, (8, 2, 1)),
+@pytest.mark.parametrize("n,want", [(2**15 - 1, (8, 4, 1)), (2**15, (4, 4, 1)), (98304, (4, 4, 1)), (98305, (8, 2, 1)),
+                                    (2**17 - 1, (8, 2, 1)), (2**17, (8, 2, 1)), (2**17 + 1, (8, 2, 1)), (161468, (8, 2, 1)), (218453, (8, 2, 1)),
                                     (218454, (4, 4, 1)), (2**18, (4, 4, 1)), (2**18 + 1, (8, 2, 1)),
                                     (2**20, (4, 4, 1))])
 def test_reported_setting_follows_the_rows(L, n, want):

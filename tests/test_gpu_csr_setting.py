@@ -8,7 +8,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [5000, 40000, 161468])
+@pytest.mark.parametrize("n", [5000, 40000, 110000, 161468])
 def test_reported_setting_is_the_one_that_runs(n):
     import torch
     if not torch.cuda.is_available():
