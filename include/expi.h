@@ -131,7 +131,10 @@ typedef struct {
                                a launch of more products counts them two by two */
     int32_t single_launches;/* single-product sweeps that did work              */
     int32_t fused_starts;   /* start vectors formed inside a pair sweep         */
-    int32_t reserved3;
+    int32_t rerun_products; /* products run twice: a loop that stopped earlier than
+                               its deferred stop tests can take the sum back to
+                               runs again.  matvecs, newton_steps and the launch
+                               counts hold the second run only               */
 } expi_stats;
 
 /* Interpolation parameters; pass NULL for the defaults

@@ -62,7 +62,7 @@ class Stats(ctypes.Structure):
                 ("fallback", ctypes.c_int32), ("finalized", ctypes.c_int32),
                 ("timed_pairs", ctypes.c_int32), ("pair_ms", ctypes.c_double),
                 ("pair_launches", ctypes.c_int32), ("single_launches", ctypes.c_int32),
-                ("fused_starts", ctypes.c_int32), ("reserved3", ctypes.c_int32)]
+                ("fused_starts", ctypes.c_int32), ("rerun_products", ctypes.c_int32)]
 
     def as_dict(self) -> dict:
         d = {name: getattr(self, name) for name, _ in self._fields_}

@@ -390,6 +390,7 @@ struct LoopOut {
     bool updated = false;          // the caller's update is already in the stream
     bool redo = false;             // the loop stopped earlier than the deferred tests can take p back
                                    // to: run it again with Ctx::defer off
+    int abandoned = 0;             // with redo: products that ran
 };
 
 struct Ctx {
@@ -609,6 +610,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         jd = open + (estimate_degree(d, C.tol, C.m_max) / 2 - open) / 4 * 4;
     }
     TestPlan plan(C);
+    std::vector<int> tested;   // products that had run at each of the deferred tests
     int finalized = 0;
     int j = 0;
     auto mod = [&](int q) { return C.di.empty() ? std::fabs(d[q]) : std::hypot(d[q], C.di[q]); };
@@ -621,6 +623,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         for (int q = 0; q < plan.products; ++q) plan.t.d[dof + q] = mod(m + q);
         plan.t.dfix = d[m + plan.products - 1];
         HIP_TRY(launch_tests(plan.t, C.s));
+        tested.push_back(m + plan.products - 1);
         // (the first value of a fused start is the start vector's norm)
         finalized += plan.products - (m == 0 ? 1 : 0);
         plan.t.m0 = m + plan.products;
@@ -1021,7 +1024,10 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         out->updated = spec && !ahead && last.done == 1;
     }
     if (last.done == 3) {
+        // the launches past the tests that found the stop did nothing
         out->redo = true;
+        for (int q : tested)
+            if (out->abandoned < last.m) out->abandoned = q;
         return EXPI_OK;
     }
     out->m = last.m;
@@ -1163,7 +1169,9 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
         const double delta = tau / sub;
         C.key = DdKey(k, delta, c, gamma, count);
         C.d = get_dd(op, C.key);
+        const int rerun = acc.rerun_products;
         acc = expi_stats{};
+        acc.rerun_products = rerun;
         acc.substeps = sub;
         acc.retries = attempt;
         acc.interval_a = ia;
@@ -1257,7 +1265,9 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
             if (rc) return rc;
             if (lo.redo) {
                 // the same substep with a stop test per launch
-                if (k == 1 && l > 0) acc.matvecs -= 1;
+                const int start = k == 1 && l > 0 ? 1 : 0;   // (its start vector is formed again)
+                acc.matvecs -= start;
+                acc.rerun_products += lo.abandoned + start;
                 again = true;
                 --l;
                 continue;
@@ -1341,7 +1351,9 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
         // the two-term estimate of the remainder is looser on long substeps
         const double len = delta * (ib - ia);
         C.tol = (learned_sub && len > P.l_max) ? tol * (P.l_max / len) : tol;
+        const int rerun = acc.rerun_products;
         acc = expi_stats{};
+        acc.rerun_products = rerun;
         acc.substeps = sub;
         acc.retries = attempt;
         acc.interval_a = ia;
@@ -1396,6 +1408,7 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
             if (lo.redo) {
                 // the same substep with a stop test per launch
                 acc.matvecs -= 1;
+                acc.rerun_products += lo.abandoned + 1;
                 if (fuse) acc.fused_starts -= 1;
                 again = true;
                 --l;
@@ -1477,7 +1490,9 @@ static int run_skew(Op& op, int k, double tau, const double* v, double* y, doubl
         // the key's k is offset so the real and complex coefficients never share a cache slot
         C.key = DdKey(1000 + k, delta, c, gamma, count);
         get_dd_skew(op, k, C.key, &C.d, &C.di);
+        const int rerun = acc.rerun_products;
         acc = expi_stats{};
+        acc.rerun_products = rerun;
         acc.substeps = sub;
         acc.retries = attempt;
         acc.interval_a = ia;
@@ -1512,7 +1527,9 @@ static int run_skew(Op& op, int k, double tau, const double* v, double* y, doubl
             if (rc) return rc;
             if (lo.redo) {
                 // the same substep with a stop test per launch
-                if (k == 1 && l > 0) acc.matvecs -= 1;
+                const int start = k == 1 && l > 0 ? 1 : 0;   // (its start vector is formed again)
+                acc.matvecs -= start;
+                acc.rerun_products += lo.abandoned + start;
                 again = true;
                 --l;
                 continue;
@@ -1579,6 +1596,7 @@ static int run_exprk2(Op& op, int nonlin, double tau, double* u, double tol, int
     acc.pair_ms += s2.pair_ms;
     acc.pair_launches += s2.pair_launches;
     acc.single_launches += s2.single_launches;
+    acc.rerun_products += s2.rerun_products;
     if (st) *st = acc;
     if (rc) return rc;
     // u <- U + tau phi_2(tau A)(g(U) - g(u_n))

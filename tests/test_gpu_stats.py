@@ -75,3 +75,26 @@ def test_tested_products_are_counted_alike(E, fuse):
         print(f"finalized {s['finalized']} of degree {s['degree_last']} (launch by launch {r['finalized']})", flush=True)
         assert s["fused_starts"] == fuse - 1 and s["degree_last"] == r["degree_last"]
         assert s["finalized"] == r["finalized"], call
+
+
+@pytest.mark.parametrize("name", ["resident", "const2d", "field2d", "const3d", "field3d", "csr"])
+def test_products_run_twice_are_reported(E, name):
+    """A much earlier stop than every known one makes the loop run again: the
+    call says how many products it ran for nothing; other calls say none."""
+    new, n = make(E, name)
+    op = new()
+    a, b = op.interval()
+    tau = 13.0 / (b - a)
+    rough, ones = T(synth.uniform_vector(n, 1)), T(np.ones(n))
+    for _ in range(8):
+        _, s = E.phi_action(op, 1, tau, rough, tol=1e-10)
+        assert s["rerun_products"] == 0
+    _, s1 = E.phi_action(op, 1, tau, ones, tol=1e-10)
+    print(f"{name}: degree {s['degree_last']}, then {s1['degree_last']}, run twice {s1['rerun_products']}", flush=True)
+    assert s1["degree_last"] == 2 and s1["matvecs"] == 2
+    if name == "resident":
+        assert s1["rerun_products"] == 0
+    else:
+        assert 2 < s1["rerun_products"] <= s["degree_last"]
+    _, s2 = E.phi_action(op, 1, tau, ones, tol=1e-10)
+    assert s2["rerun_products"] == 0
