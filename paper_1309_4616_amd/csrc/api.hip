@@ -329,18 +329,19 @@ int get_hint(Op& op, const DdKey& key) {
     return it == op.degree_hint.end() ? 0 : it->second;
 }
 
-// Degrees differ from substep to substep of a call (later ones start from
-// smoother vectors), so each has a hint of its own; it shares the map through
-// the coefficient count, which is at most kMaxLeja.
-DdKey substep_key(DdKey key, int l) {
-    std::get<4>(key) += (kMaxLeja + 1) * (1 + std::min(l, 63));
-    return key;
-}
-
 void set_hint(Op& op, const DdKey& key, int m) {
     std::lock_guard<std::mutex> lock(op.mu);
     if (op.degree_hint.size() > 1024) op.degree_hint.clear();
     op.degree_hint[key] = m;
+}
+
+// Degrees differ from substep to substep of a call (later ones start from
+// smoother vectors), from tolerance to tolerance and with the storage type, so
+// each has a record of its own; the substep shares the key through the
+// coefficient count, which is at most kMaxLeja.
+DegreeKey degree_key(DdKey key, int l, double tol, int tw) {
+    std::get<4>(key) += (kMaxLeja + 1) * (1 + std::min(l, 63));
+    return DegreeKey(key, tol, tw);
 }
 
 // The lowest degree seen lately.  Tests are deferred no further than that: a
@@ -351,16 +352,17 @@ void set_hint(Op& op, const DdKey& key, int m) {
 // degree cost one stop test each.
 constexpr int kDegreeWindow = 16;
 
-int get_low(Op& op, const DdKey& key) {
+DegreeWindow get_degrees(Op& op, const DegreeKey& key) {
     std::lock_guard<std::mutex> lock(op.mu);
-    auto it = op.degree_low.find(key);
-    return it == op.degree_low.end() ? 0 : it->second.low;
+    auto it = op.degrees.find(key);
+    return it == op.degrees.end() ? DegreeWindow() : it->second;
 }
 
-void set_low(Op& op, const DdKey& key, int m) {
+void add_degree(Op& op, const DegreeKey& key, int m) {
     std::lock_guard<std::mutex> lock(op.mu);
-    if (op.degree_low.size() > 1024) op.degree_low.clear();
-    DegreeWindow& w = op.degree_low[key];
+    if (op.degrees.size() > 1024) op.degrees.clear();
+    DegreeWindow& w = op.degrees[key];
+    w.last = m;
     w.low = w.low ? std::min(w.low, m) : m;
     w.next = w.count ? std::min(w.next, m) : m;
     if (++w.count >= kDegreeWindow) {
@@ -589,8 +591,9 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     // products sum their norms in different orders, so 3D pairs are laid out
     // for the degree of the last loop of this length, whichever substep it
     // was, and only their tests are deferred.
-    const int expected = get_low(*C.op, substep_key(C.key, C.substep));
-    const int own_degree = get_hint(*C.op, substep_key(C.key, C.substep));
+    const DegreeKey degree_of = degree_key(C.key, C.substep, C.tol, C.tw);
+    const DegreeWindow seen = get_degrees(*C.op, degree_of);
+    const int expected = seen.low, own_degree = seen.last;
     const int last_degree = get_hint(*C.op, C.key);
     const int group = (own_degree >= 2 && (C.chains || !C.pairs)) ? own_degree : last_degree;
     const bool defer_on = C.defer && !C.profile && !C.selector;
@@ -1045,8 +1048,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     }
     if (last.done == 1) {
         set_hint(*C.op, C.key, last.m);
-        set_hint(*C.op, substep_key(C.key, C.substep), last.m);
-        set_low(*C.op, substep_key(C.key, C.substep), last.m);
+        add_degree(*C.op, degree_of, last.m);
     }
     if (last.done != 2) {
         // launches that began before the stop did work (the opening ones

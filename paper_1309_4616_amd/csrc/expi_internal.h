@@ -245,12 +245,17 @@ struct Geom {
     int flat;             // 3D stencils: rows end to end (SweepArgs::flat)
 };
 
-// Lowest Newton degree of the last kDegreeWindow to 2 kDegreeWindow loops.
+// Newton degrees of the loops with one DegreeKey: the last one, and the lowest
+// of the last kDegreeWindow to 2 kDegreeWindow.
 struct DegreeWindow {
+    int last = 0;
     int low = 0;      // of the window before and of this one
     int next = 0;     // of this window
     int count = 0;    // loops in this window
 };
+// What the degree depends on besides the vectors: the coefficients' key (its
+// last entry coded with the substep), the tolerance and the storage type.
+typedef std::tuple<std::tuple<int, double, double, double, int>, double, int> DegreeKey;
 
 struct Op {
     int kind;             // 0 stencil, 1 CSR, 2 complex CSR (val: complex128 pairs)
@@ -278,7 +283,7 @@ struct Op {
     std::map<std::tuple<int, double, double, double, int>, std::vector<double>> dd_cache;
     // Newton degree last seen for a key, used to size the first chunk
     std::map<std::tuple<int, double, double, double, int>, int> degree_hint;
-    std::map<std::tuple<int, double, double, double, int>, DegreeWindow> degree_low;
+    std::map<DegreeKey, DegreeWindow> degrees;
 };
 
 constexpr int kXcd = 8;          // XCDs of gfx950; workgroup b runs on XCD b % 8

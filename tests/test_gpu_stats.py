@@ -98,3 +98,22 @@ def test_products_run_twice_are_reported(E, name):
         assert 2 < s1["rerun_products"] <= s["degree_last"]
     _, s2 = E.phi_action(op, 1, tau, ones, tol=1e-10)
     assert s2["rerun_products"] == 0
+
+
+@pytest.mark.parametrize("name", ["const2d", "field2d", "const3d", "field3d", "csr"])
+def test_tolerances_and_storage_types_learn_apart(E, name):
+    """Degrees known from a tight tolerance or from FP64 say nothing about a
+    loose one or FP32: no such call runs its loop twice."""
+    new, n = make(E, name)
+    op = new()
+    a, b = op.interval()
+    tau = 13.0 / (b - a)
+    v = T(synth.uniform_vector(n, 1))
+    degrees = set()
+    for tol, dtype in ((1e-12, "f64"), (1e-3, "f64"), (1e-12, "f64"), (1e-6, "f32"), (1e-3, "f32")):
+        for _ in range(8):
+            _, s = E.phi_action(op, 1, tau, v, tol=tol, dtype=dtype)
+            assert s["rerun_products"] == 0, (tol, dtype)
+        degrees.add(s["degree_last"])
+        print(f"{name} tol {tol} {dtype}: degree {s['degree_last']}", flush=True)
+    assert len(degrees) >= 3
