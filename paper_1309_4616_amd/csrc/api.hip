@@ -345,12 +345,18 @@ DegreeKey degree_key(DdKey key, int l, double tol, int tw) {
 }
 
 // The lowest degree seen lately.  Tests are deferred no further than that: a
-// loop that stops before them is run again launch by launch, about twice its
-// work, so inputs whose degree goes up and down must not cause it each time.
-// With degrees in random order a loop is lower than all of the last 16 or more
-// at most once in 17; the tested launches between the lowest and the usual
-// degree cost one stop test each.
+// loop that stops before them is run again, about twice its work, so inputs
+// whose degree goes up and down must not cause it each time.  With degrees in
+// random order a loop is lower than all of the last 16 or more at most once in
+// 17; the tested launches between the lowest and the usual degree cost one
+// stop test each.
 constexpr int kDegreeWindow = 16;
+// Loops that have to be seen first.  After c degrees in random order the next
+// is lower than all of them once in c + 1 times: from 4 on, the loops run twice
+// (1.3 of the next 12, at less than their time once more) cost no more than the
+// deferred tests give on small operators (9% of a call), and a degree known
+// from one other vector costs nothing.
+constexpr int kDegreeLoops = 4;
 
 DegreeWindow get_degrees(Op& op, const DegreeKey& key) {
     std::lock_guard<std::mutex> lock(op.mu);
@@ -365,6 +371,7 @@ void add_degree(Op& op, const DegreeKey& key, int m) {
     w.last = m;
     w.low = w.low ? std::min(w.low, m) : m;
     w.next = w.count ? std::min(w.next, m) : m;
+    w.loops = std::min(w.loops + 1, kDegreeLoops);
     if (++w.count >= kDegreeWindow) {
         w.low = w.next;
         w.count = 0;
@@ -390,8 +397,8 @@ struct LoopOut {
     double fix = 0;       // p holds d_{m+1} w_{m+1} too many (pair stopped at its first product)
     const void* fix_w = nullptr;   // where w_{m+1} is
     bool updated = false;          // the caller's update is already in the stream
-    bool redo = false;             // the loop stopped earlier than the deferred tests can take p back
-                                   // to: run it again with Ctx::defer off
+    bool redo = false;             // the loop stopped at m, earlier than the deferred tests can take p
+                                   // back to: run it again with Ctx::known = this
     int abandoned = 0;             // with redo: products that ran
 };
 
@@ -426,6 +433,9 @@ struct Ctx {
     // an earlier loop, and chains of products on 2D stencils; `spare` is
     // workspace this loop may use for partials besides its own region
     bool defer = false;
+    // what the loop's first run found (LoopOut::redo): the same products up to
+    // that degree without tests
+    const LoopOut* known = nullptr;
     bool chains = false;
     bool resident = false;   // the whole loop in one workgroup
     char* spare = nullptr;
@@ -441,14 +451,17 @@ struct TestPlan {
     size_t used = 0, used_spare = 0, cap;
     size_t room;           // the larger of the two: what one launch may take
     int products = 0;
+    bool untested;         // launches only write their partials somewhere
     explicit TestPlan(const Ctx& c) : C(c), cap(partials_bytes(*c.op)), room(std::max(cap, c.spare_bytes)) {
         t.st = c.st;
         t.tol = c.tol;
         t.roff = -1;
+        untested = c.known != nullptr;
     }
     // a place for `bytes` of partials (null: none left)
     double* place(size_t bytes, int n) {
         bytes = align256(bytes);
+        if (untested) used = used_spare = 0;
         if (t.launches >= kMaxTestLaunches || products + n > kMaxTestProducts) return nullptr;
         if (used + bytes <= cap) {
             used += bytes;
@@ -461,6 +474,7 @@ struct TestPlan {
         return nullptr;
     }
     void add(const double* part, int nparts, int stride, int off, int n) {
+        if (untested) return;
         t.l[t.launches++] = TestLaunch{part, nparts, stride, off, n};
         products += n;
     }
@@ -580,37 +594,48 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     // storage type and alignment the pair sweep reads (w_2 goes to w[0]:
     // `src` may be w[1]).  Otherwise product 0 alone.
     const bool first_pair = C.pairs && C.m_max >= 3 && tin == C.tw && (((uintptr_t)src & 15) == 0);
-    // With a degree hint, the products up to the last launch before it run
+    // With a known degree, the products up to the last launch before it run
     // without a test each (their norms are kept) and are tested together:
-    // jd is where the tested launches begin.  Without one, only chains of
-    // products are tested together, up to half the estimated degree.
-    // expected: the lowest degree this substep stopped at lately; no test at
-    // or past it is deferred.  group: the degree the launches are laid out
-    // for, that of the last time.  A stop at the first product of a
+    // jd is where the tested launches begin.  expected: the lowest degree this
+    // substep stopped at lately; no test at or past it is deferred.  Without
+    // one that is sure (kDegreeLoops), chains of products are tested each, up
+    // to where the loop is expected to stop or to half the estimated degree.
+    // group: the degree the launches are laid out for, that of the last time.
+    // A stop at the first product of a
     // pair leaves a rounding of the extra term in p, and pairs and single
     // products sum their norms in different orders, so 3D pairs are laid out
     // for the degree of the last loop of this length, whichever substep it
     // was, and only their tests are deferred.
     const DegreeKey degree_of = degree_key(C.key, C.substep, C.tol, C.tw);
     const DegreeWindow seen = get_degrees(*C.op, degree_of);
+    const bool sure = seen.loops >= kDegreeLoops;
     const int expected = seen.low, own_degree = seen.last;
     const int last_degree = get_hint(*C.op, C.key);
     const int group = (own_degree >= 2 && (C.chains || !C.pairs)) ? own_degree : last_degree;
     const bool defer_on = C.defer && !C.profile && !C.selector;
     const bool chain_first = defer_on && C.chains && !start_u && tin == C.tw && C.m_max >= 6;
+    const bool known = C.known != nullptr;
     int jd = 0;
-    bool each = false;   // a test after every deferred launch
-    if (defer_on && expected >= 2 && group >= 2) {
+    bool each = false;   // a test after every chain
+    if (known) {
+        jd = C.known->m;
+    } else if (defer_on && expected >= 2 && group >= 2 && (sure || C.chains)) {
         const int open = (start_u || !(first_pair || chain_first)) ? 1 : 2;
         const int end = std::min(group, C.m_max);
         jd = end - ((C.pairs && (C.chains || (end - open) % 2 == 0)) ? 2 : 1);
         if (expected < end) jd = std::min(jd, C.pairs ? open + (expected - 1 - open) / 2 * 2 : expected - 1);
         // (without chains of 5, chains take an even count)
         if (C.chains && !chain2d_length(*C.op, 5) && (jd - (open == 2 ? 0 : 1)) % 2 != 0) --jd;
+        each = !sure;
     } else if (defer_on && C.chains) {
         each = true;
-        const int open = chain_first ? 0 : 1;
-        jd = open + (estimate_degree(d, C.tol, C.m_max) / 2 - open) / 4 * 4;
+        jd = estimate_degree(d, C.tol, C.m_max) / 2;
+    }
+    if (each) {
+        // products 0 and 1 with tests (nearly constant vectors stop there),
+        // then chains of four
+        jd = jd >= 6 ? 2 + (jd - 2) / 4 * 4 : 0;
+        each = jd > 0;
     }
     TestPlan plan(C);
     std::vector<int> tested;   // products that had run at each of the deferred tests
@@ -661,7 +686,8 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         if (b.first) plan.t.roff = 0;
         else cur ^= 1;
         plan.add(part, np, 16, 1, n);
-        plan.t.pair_last = n == 2;
+        // (FP32 sums keep the bits of single products: such a stop runs again)
+        plan.t.pair_last = n == 2 && (C.pairs || C.tw == 0);
         plan.t.outbuf = cur;
         log.push_back({j, n, w[cur], false});
         return EXPI_OK;
@@ -669,19 +695,19 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     // Pairs of a constant-coefficient 2D stencil are chains of two (FP64): a
     // product then rounds the same however the launches are grouped.
     const bool chain_pairs = C.chains && C.pairs && !C.profile && !C.selector;
-    const bool chain_open = chain_first && jd >= 4;
-    if (!chain_open && chain_pairs && first_pair) {
+    const bool chain_open = chain_first && (known ? jd >= 2 : jd >= 4 && !each);
+    if (!chain_open && ((chain_pairs && first_pair) || (each && chain_first))) {
         bool ok = true;
         int rc = chain(0, 2, &ok);
         if (rc) return rc;
         if (!ok) return fail(EXPI_EHIP, "internal: no room for a chain's partials");
         j = 2;
-        if (jd <= 2) rc = flush();
+        if (jd <= 2 || each) rc = flush();
         if (rc) return rc;
     } else if (!chain_open) {
         double* part0 = C.partials;
         bool fin0 = true;
-        if (jd > 2) {
+        if (known || (jd > 2 && !each)) {
             // the opening launch joins the deferred tests
             part0 = plan.place(!(start_u || first_pair) ? single_partials(*C.op, C.tw)
                                : C.op->dim == 2         ? pair2d_partials(*C.op)
@@ -753,7 +779,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
             plan.t.m0 = j + 1;
             plan.t.roff = -1;
             plan.t.cont = 1;
-            if (!C.chains || !each) jd = 0;
+            if (!each) jd = 0;
         }
     }
 
@@ -857,6 +883,11 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         return wait_slot(slot, st);
     };
 
+    if (each && j == 1) {
+        const int rc = single(1, true);
+        if (rc) return rc;
+        j = 2;
+    }
     // the deferred part: products up to jd
     while (j < jd) {
         int rc;
@@ -870,7 +901,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
             if (six && left >= 6 && left != 8 && left != 7 && left != 9) n = 6;
             else if (six && (left == 5 || left == 7 || left == 9)) n = 5;
             else if (left >= 4) n = 4;
-            else if (left >= 2 && j > 0) n = 2;
+            else if (left >= 2 && (j > 0 || known)) n = 2;
             if (n) {
                 rc = chain(j, n, &ok);
                 if (rc) return rc;
@@ -909,6 +940,30 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         if (rc) return rc;
     }
     a.partials = C.partials;
+
+    // launches that began before the stop did work (the opening ones always
+    // do); later ones returned at once
+    auto count_launches = [&](int m) {
+        for (const Launch& L : log) {
+            if (L.j >= m && L.j > 0) continue;
+            // (a chain counts its products two by two)
+            if (L.n >= 2) out->pair_launches += L.n / 2;
+            else ++out->single_launches;
+        }
+    };
+    auto learn = [&](int m) {
+        set_hint(*C.op, C.key, m);
+        add_degree(*C.op, degree_of, m);
+    };
+    if (known) {
+        if (j != jd) return fail(EXPI_EHIP, "internal: products missing from a loop run again");
+        HIP_TRY(launch_accept(C.st, C.s));
+        *out = *C.known;
+        out->redo = false;
+        learn(jd);
+        count_launches(jd);
+        return EXPI_OK;
+    }
 
     NewtonState last{};
     bool finished = false;
@@ -1026,19 +1081,21 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         }
         out->updated = spec && !ahead && last.done == 1;
     }
-    if (last.done == 3) {
-        // the launches past the tests that found the stop did nothing
-        out->redo = true;
-        for (int q : tested)
-            if (out->abandoned < last.m) out->abandoned = q;
-        return EXPI_OK;
-    }
     out->m = last.m;
     out->done = last.done;
     out->err = last.err;
     out->rnorm = last.rnorm;
     for (int q = 0; q < kHist; ++q) out->hist[q] = last.hist[q];
     out->finalized = finalized;
+    if (last.done == 3) {
+        // the launches past the tests that found the stop did nothing
+        out->redo = true;
+        out->done = 1;
+        for (int q : tested)
+            if (out->abandoned < last.m) out->abandoned = q;
+        out->finalized = out->abandoned;
+        return EXPI_OK;
+    }
     if (last.done == 1 && last.fix != 0.0) {
         // the pair sweep at m - 1 wrote w_{m+1}
         for (const Launch& L : log)
@@ -1046,20 +1103,8 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         if (!out->fix_w) return fail(EXPI_EHIP, "internal: no pair sweep for the stop at m");
         out->fix = last.fix;
     }
-    if (last.done == 1) {
-        set_hint(*C.op, C.key, last.m);
-        add_degree(*C.op, degree_of, last.m);
-    }
-    if (last.done != 2) {
-        // launches that began before the stop did work (the opening ones
-        // always do); later ones returned at once
-        for (const Launch& L : log) {
-            if (L.j >= last.m && L.j > 0) continue;
-            // (a chain counts its products two by two)
-            if (L.n >= 2) out->pair_launches += L.n / 2;
-            else ++out->single_launches;
-        }
-    }
+    if (last.done == 1) learn(last.m);
+    if (last.done != 2) count_launches(last.m);
     if (C.profile && last.done != 2) {
         // launches that began before the stop did work and precede the read-back
         for (const Launch& L : log) {
@@ -1182,7 +1227,8 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
         C.chains = P.pairs && op.use_pairs != 0 && chain2d_supported(op, tw);
         C.resident = C.chains && !P.profile && !P.selector && resident2d_supported(op, tw, P.m_max);
         if (!C.resident) HIP_TRY(launch_reset(C.st, s));
-        bool ok = true, again = false;
+        bool ok = true;
+        LoopOut stop;   // a loop to be run again
         for (int l = 0; l < sub && ok; ++l) {
             // p goes straight into y when y is the result and has p's type
             const bool p_in_y = (sub == 1 && tw == 0);
@@ -1253,9 +1299,9 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
             C.spare_bytes = y_slot ? (size_t)n * 8 : 0;
             // (a substep of phi_k, k >= 2, adds to y while it forms its start
             // vector, so it cannot be run again)
-            C.defer = !again && !(phik_sub && l > 0);
+            C.defer = !(phik_sub && l > 0);
             C.substep = l;
-            again = false;
+            C.known = stop.redo ? &stop : nullptr;
             // the update of this substep, enqueued ahead of the status
             // read-back where it always runs (p_in_y needs one only for a fix)
             const double* yin = ((k == 1 || phik_sub) && l > 0) ? y : nullptr;
@@ -1266,14 +1312,15 @@ static int run_phi(Op& op, int k, double tau, const double* v, double* y, double
             rc = newton_loop(C, src, tin, p, &lo, false, p_in_y ? nullptr : &spec);
             if (rc) return rc;
             if (lo.redo) {
-                // the same substep with a stop test per launch
+                // the same substep up to the degree found
                 const int start = k == 1 && l > 0 ? 1 : 0;   // (its start vector is formed again)
                 acc.matvecs -= start;
                 acc.rerun_products += lo.abandoned + start;
-                again = true;
+                stop = lo;
                 --l;
                 continue;
             }
+            stop.redo = false;
             stats_add(&acc, lo);
             if (lo.done == 2) return fail(EXPI_ENONFINITE, "a norm became inf/NaN (non-finite input?)");
             if (lo.done != 1) {
@@ -1361,7 +1408,8 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
         acc.interval_a = ia;
         acc.interval_b = ib;
         HIP_TRY(launch_reset(C.st, s));
-        bool ok = true, again = false;
+        bool ok = true;
+        LoopOut stop;   // a loop to be run again
         int restart = 0;
         for (int l = 0; l < sub && ok; ++l) {
             // r = A y_l + g(u), y_0 = u: its own sweep, or (first substep)
@@ -1388,9 +1436,9 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
             C.resident = C.chains && !P.profile && !P.selector && resident2d_supported(op, tw, P.m_max);
             C.spare = sub == 1 ? ws + L.y : nullptr;   // y_l lives there otherwise
             C.spare_bytes = sub == 1 ? (size_t)n * 8 : 0;
-            C.defer = !again;
+            C.defer = true;
             C.substep = l;
-            again = false;
+            C.known = stop.redo ? &stop : nullptr;
             if (fuse) {
                 rc = newton_loop(C, u, 0, p, &lo, true, &spec);
                 acc.fused_starts += 1;
@@ -1408,11 +1456,11 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
             }
             if (rc) return rc;
             if (lo.redo) {
-                // the same substep with a stop test per launch
+                // the same substep up to the degree found
                 acc.matvecs -= 1;
                 acc.rerun_products += lo.abandoned + 1;
                 if (fuse) acc.fused_starts -= 1;
-                again = true;
+                stop = lo;
                 --l;
                 continue;
             }
@@ -1426,6 +1474,7 @@ static int run_expeuler(Op& op, int nonlin, double tau, double* u, double tol, i
                 wasted_fin = lo.finalized;
                 break;
             }
+            stop.redo = false;
             stats_add(&acc, lo);
             if (lo.done == 2) return fail(EXPI_ENONFINITE, "a norm became inf/NaN (non-finite input?)");
             if (lo.done != 1) {
@@ -1500,7 +1549,8 @@ static int run_skew(Op& op, int k, double tau, const double* v, double* y, doubl
         acc.interval_a = ia;
         acc.interval_b = ib;
         HIP_TRY(launch_reset(C.st, s));
-        bool ok = true, again = false;
+        bool ok = true;
+        LoopOut stop;   // a loop to be run again
         C.spare = ws + L.y;   // not used otherwise
         C.spare_bytes = (size_t)nd * 8;
         for (int l = 0; l < sub && ok; ++l) {
@@ -1522,20 +1572,21 @@ static int run_skew(Op& op, int k, double tau, const double* v, double* y, doubl
                 src = y;
             }
             LoopOut lo;
-            C.defer = !again;
+            C.defer = true;
             C.substep = l;
-            again = false;
+            C.known = stop.redo ? &stop : nullptr;
             rc = newton_loop(C, src, 0, p, &lo);
             if (rc) return rc;
             if (lo.redo) {
-                // the same substep with a stop test per launch
+                // the same substep up to the degree found
                 const int start = k == 1 && l > 0 ? 1 : 0;   // (its start vector is formed again)
                 acc.matvecs -= start;
                 acc.rerun_products += lo.abandoned + start;
-                again = true;
+                stop = lo;
                 --l;
                 continue;
             }
+            stop.redo = false;
             stats_add(&acc, lo);
             if (lo.done == 2) return fail(EXPI_ENONFINITE, "a norm became inf/NaN (non-finite input?)");
             if (lo.done != 1) {

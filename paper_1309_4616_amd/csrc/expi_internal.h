@@ -25,7 +25,7 @@ constexpr int kMaxPairWaves = 16;   // waves of a pair-sweep workgroup
 struct alignas(64) NewtonState {
     unsigned int arrive;  // reserved
     int done;             // 0 running, 1 stop test met, 2 non-finite norm, 3 stop test met earlier than p
-                          // can be taken back to (deferred tests): run the loop again
+                          // can be taken back to (deferred tests): run the loop again up to m
     int m;                // products taken in this loop
     int fixbuf;           // with fix: which of the two w buffers holds w_{m+1}
     double t_prev;        // |d_m| ||w_m|| of the latest product
@@ -252,6 +252,7 @@ struct DegreeWindow {
     int low = 0;      // of the window before and of this one
     int next = 0;     // of this window
     int count = 0;    // loops in this window
+    int loops = 0;    // loops seen, counted up to kDegreeLoops
 };
 // What the degree depends on besides the vectors: the coefficients' key (its
 // last entry coded with the substep), the tolerance and the storage type.
@@ -363,8 +364,10 @@ size_t pair2d_partials(const Op& op);
 // The stop tests of the launches in `t`, in order of their products: the
 // state as the finalize kernels of the launches would have left it.  A stop
 // that leaves later terms in p (other than the one a pair sweep leaves) is
-// recorded as done = 3: the loop has to be run again with a test per launch.
+// recorded as done = 3: the loop has to be run again, without tests, up to m.
 hipError_t launch_tests(TestArgs& t, hipStream_t s);
+// done = 3 becomes 1: the loop has been run again up to m.
+hipError_t launch_accept(NewtonState* st, hipStream_t s);
 hipError_t launch_fill(void* out, int64_t n, int t, double scale, hipStream_t s);
 // The boundary term of a stencil's Dirichlet data over its boundary layer
 // (boundary.hip): y += scale * b_f, y of storage code t.

@@ -256,6 +256,13 @@ __global__ __launch_bounds__(kTestThreads) void tests_kernel(TestArgs f) {
     }
 }
 
+__global__ void accept_kernel(NewtonState* st) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) {
+        st->fix = 0.0;
+        st->done = 1;
+    }
+}
+
 __global__ void reset_kernel(NewtonState* st) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         st->arrive = 0;
@@ -548,6 +555,11 @@ hipError_t launch_tests(TestArgs& t, hipStream_t s) {
     if (t.launches < 1 || t.launches > kMaxTestLaunches || total > kMaxTestProducts) return hipErrorInvalidValue;
     t.mirror = tl_mirror;
     hipLaunchKernelGGL(tests_kernel, dim3(1), dim3(kTestThreads), 0, s, t);
+    return hipGetLastError();
+}
+
+hipError_t launch_accept(NewtonState* st, hipStream_t s) {
+    hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(64), 0, s, st);
     return hipGetLastError();
 }
 
