@@ -692,17 +692,17 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         log.push_back({j, n, w[cur], false});
         return EXPI_OK;
     };
-    // Pairs of a constant-coefficient 2D stencil are chains of two (FP64): a
-    // product then rounds the same however the launches are grouped.
-    const bool chain_pairs = C.chains && C.pairs && !C.profile && !C.selector;
+    // Products 0 and 1 as a chain of two where the loop is laid out in chains
+    // (a pair sweep that is tested by itself is no chain: it takes 424 us at
+    // 8192^2 FP64, a chain of two 467; the two round alike).
     const bool chain_open = chain_first && (known ? jd >= 2 : jd >= 4 && !each);
-    if (!chain_open && ((chain_pairs && first_pair) || (each && chain_first))) {
+    if (!chain_open && chain_first && (each ? !first_pair : first_pair && jd > 2)) {
         bool ok = true;
         int rc = chain(0, 2, &ok);
         if (rc) return rc;
         if (!ok) return fail(EXPI_EHIP, "internal: no room for a chain's partials");
         j = 2;
-        if (jd <= 2 || each) rc = flush();
+        if (each) rc = flush();
         if (rc) return rc;
     } else if (!chain_open) {
         double* part0 = C.partials;
@@ -811,13 +811,6 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     };
     // products j and j+1 in one pair sweep
     auto pair = [&](int j, bool fin, double* part = nullptr) -> int {
-        if (chain_pairs) {
-            bool ok = true;
-            const int rc = chain(j, 2, &ok);
-            if (rc) return rc;
-            if (!ok) return fail(EXPI_EHIP, "internal: no room for a chain's partials");
-            return fin ? flush() : EXPI_OK;
-        }
         int np = 0;
         PairArgs b{};
         b.x = w[cur];

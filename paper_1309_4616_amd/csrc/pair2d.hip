@@ -121,17 +121,26 @@ __device__ void pair2d_tile(const PairArgs& a, int t0, int t1, int march, double
         xb[v] = IO && !(em && eq);
         axm[v] = em ? alpha * fx : (TC)0;
         axq[v] = eq ? alpha * fx : (TC)0;
-        adx[v] = alpha * (((em || dir) ? fx : (TC)0) + ((eq || dir) ? fx : (TC)0));
+        adx[v] = alpha * (((em || dir) ? fx : (TC)0) + ((eq || dir) ? fx : (TC)0));   // (exact doubling)
     }
+    // FP64 products and sums are written out as those of the chain sweeps
+    // (chain2d.h), so that a result does not depend on which of the two takes
+    // a product
+    constexpr bool kFixed = std::is_same<TW, double>::value;
     auto yw = [&](int q, TC beta, TC& aym, TC& ayq, TC& cdy, bool& rb) {
         const bool em = q > 0, eq = q < n1 - 1;
         rb = IO && !(em && eq);   // IO: a point of the outermost rows
         aym = em ? alpha * fy : (TC)0;
         ayq = eq ? alpha * fy : (TC)0;
-        cdy = beta - alpha * (((em || dir) ? fy : (TC)0) + ((eq || dir) ? fy : (TC)0));
+        if constexpr (kFixed) cdy = minus<TC>(beta, diag_part<TC>(alpha * fy, em || dir, eq || dir));
+        else cdy = beta - alpha * (((em || dir) ? fy : (TC)0) + ((eq || dir) ? fy : (TC)0));
     };
     auto prod = [&](int v, TC wl, TC wr, TC wm, TC wq, TC wc, TC aym, TC ayq, TC cdy, TC beta, bool rb) -> TC {
-        const TC u = axm[v] * wl + axq[v] * wr + aym * wm + ayq * wq + (cdy - adx[v]) * wc;
+        TC u;
+        if constexpr (kFixed)
+            u = const_product<TC>(axm[v], axq[v], aym, ayq, minus<TC>(cdy, adx[v]), wl, wr, wm, wq, wc);
+        else
+            u = axm[v] * wl + axq[v] * wr + aym * wm + ayq * wq + (cdy - adx[v]) * wc;
         if constexpr (IO) return (xb[v] || rb) ? beta * wc : u;
         else return u;
     };
@@ -206,10 +215,16 @@ __device__ void pair2d_tile(const PairArgs& a, int t0, int t1, int march, double
                 const TC wl = (v > 0) ? uc[v - 1] : left;
                 const TC wr = (v < V - 1) ? uc[v + 1] : right;
                 const TC u2 = (TC)(TW)prod(v, wl, wr, um[v], uq[v], uc[v], aym, ayq, cdy, beta2, rb);
-                TC p1;
-                if constexpr (kFirst) p1 = (TC)(TW)(d0 * wk[v] + d1 * uc[v]);
-                else p1 = (TC)(TW)(P[st & 3][v] + d1 * uc[v]);
-                const TC p2 = (TC)(TW)(p1 + d2 * u2);
+                TC p1, p2;
+                if constexpr (kFixed) {
+                    p1 = kFirst ? __builtin_elementwise_fma(d0, wk[v], d1 * uc[v])
+                                : __builtin_elementwise_fma(d1, uc[v], P[st & 3][v]);
+                    p2 = __builtin_elementwise_fma(d2, u2, p1);
+                } else {
+                    if constexpr (kFirst) p1 = (TC)(TW)(d0 * wk[v] + d1 * uc[v]);
+                    else p1 = (TC)(TW)(P[st & 3][v] + d1 * uc[v]);
+                    p2 = (TC)(TW)(p1 + d2 * u2);
+                }
                 wo[v] = u2;
                 po[v] = p2;
                 if (active && valid) {
