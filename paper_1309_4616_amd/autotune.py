@@ -74,6 +74,8 @@ def load(op, dtype: str = "f64", path: str | None = None) -> bool:
 def _apply(op, entry: dict) -> None:
     op.set_tiles(*entry["tiles"])
     if "pairs" in entry and hasattr(op, "set_pairs"):
+        if entry["pairs"] is None:   # no pair sweep was timed: nothing was chosen
+            return
         rows = entry.get("pair_rows")
         op.set_pairs(int(rows) if (entry["pairs"] and rows) else bool(entry["pairs"]))
 
