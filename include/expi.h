@@ -269,7 +269,9 @@ int expi_op_get_tiles(const expi_op *op, int *vec, int *waves, int *march);
  * rows (with 1 the height follows the grid size: 16 rows, fewer where the
  * grid has too few tiles for the device).  EXPI_EINVAL for other values.
  * 0 also turns off the passes of more than two products on 2D stencils of
- * any coefficient kind.
+ * any coefficient kind, and the loop in one launch on small grids; the height
+ * is that of the pair sweeps, which in FP64 take the products that are tested
+ * launch by launch.
  * expi_op_get_pairs returns the stored value (0, 1 or a row count). */
 int expi_op_set_pairs(expi_op *op, int use);
 int expi_op_get_pairs(const expi_op *op, int *use);
@@ -286,7 +288,8 @@ int expi_op_get_pairs(const expi_op *op, int *use);
  * sweep is timed at tile heights 4, 8, 16 and, where the grid has the
  * rows, 32 and 64 (listed as (0, rows, 2)); the pair setting becomes the
  * fastest height if that one takes less per product than the best single
- * product, else 0.  The
+ * product, or if the passes of more products that 0 would turn off do (they
+ * are timed and not listed), else 0.  The
  * workspace (expi_workspace_bytes(op, dtype)) supplies the vectors and is
  * overwritten.  If cand/us are given, the first max_cand tried settings
  * (vec, waves, march triples) and their mean microseconds per launch are

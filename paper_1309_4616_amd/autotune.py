@@ -76,6 +76,10 @@ def _apply(op, entry: dict) -> None:
     if "pairs" in entry and hasattr(op, "set_pairs"):
         if entry["pairs"] is None:   # no pair sweep was timed: nothing was chosen
             return
+        # (single products of a 2D operator from before its passes of several
+        # products were timed too say nothing about those)
+        if entry["pairs"] is False and len(getattr(op, "shape", ())) == 2 and not entry.get("passes_timed"):
+            return
         rows = entry.get("pair_rows")
         op.set_pairs(int(rows) if (entry["pairs"] and rows) else bool(entry["pairs"]))
 
@@ -112,7 +116,7 @@ def tune(op, dtype: str = "f64", reps: int = 10, path: str | None = None,
     paired = any(c[0] == 0 for c, _ in rows)
     entry = {"tiles": list(best), "us": min(singles) if singles else None,
              "pairs": (op.pairs() if paired else None),
-             "candidates": [[list(c), t] for c, t in rows]}
+             "passes_timed": paired, "candidates": [[list(c), t] for c, t in rows]}
     if paired and op.pair_setting() > 1:
         entry["pair_rows"] = op.pair_setting()   # the 2D pair sweep's tile height
     if use_cache:

@@ -1965,19 +1965,22 @@ int expi_op_autotune(expi_op* op, int dtype, int reps, void* ws, size_t ws_bytes
             for (int r = 4; r <= 64; r *= 2)
                 if (r <= 16 || r / 2 < o.n[1]) heights.push_back(r);
         }
-        float best_pair = 1e30f;
-        int best_rows = 1;
-        for (int rows : heights) {
-            err = launch_pair_op(o, tw, b, s, nullptr, false, PAIR_NEWTON, rows);   // warm up
+        // microseconds per launch (after one to warm up), 1e30 if it failed
+        auto time_us = [&](const std::function<hipError_t()>& launch) -> float {
+            err = launch();
             if (err == hipSuccess) err = hipEventRecord(e0, s);
-            for (int r = 0; r < reps && err == hipSuccess; ++r)
-                err = launch_pair_op(o, tw, b, s, nullptr, false, PAIR_NEWTON, rows);
+            for (int r = 0; r < reps && err == hipSuccess; ++r) err = launch();
             if (err == hipSuccess) err = hipEventRecord(e1, s);
             if (err == hipSuccess) err = hipEventSynchronize(e1);
             float ms = 0.f;
             if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+            return err == hipSuccess ? 1e3f * ms / reps : 1e30f;
+        };
+        float best_pair = 1e30f;
+        int best_rows = 1;
+        for (int rows : heights) {
+            const float per = time_us([&] { return launch_pair_op(o, tw, b, s, nullptr, false, PAIR_NEWTON, rows); });
             if (err != hipSuccess) break;
-            const float per = 1e3f * ms / reps;
             if (nc < max_cand && cand && us) {
                 cand[3 * nc] = 0;
                 cand[3 * nc + 1] = rows;
@@ -1990,7 +1993,46 @@ int expi_op_autotune(expi_op* op, int dtype, int reps, void* ws, size_t ws_bytes
                 best_rows = rows ? rows : 1;
             }
         }
-        if (err == hipSuccess) use_pairs = (0.5f * best_pair < best_us) ? best_rows : 0;
+        // single products only if nothing that the setting also turns off
+        // takes less: the longest chain, or the loop in one workgroup
+        float passes = 0.5f * best_pair;
+        if (err == hipSuccess && chain2d_supported(o, tw)) {
+            // |alpha A| <= 1, so that a loop of many products stays finite
+            double norm = 0.0;
+            for (int q = 0; q < 2; ++q) norm += 4.0 * std::fabs(o.c0) / (o.h[q] * o.h[q]);
+            const double alpha = norm > 0.0 ? 1.0 / norm : 0.0;
+            const int m = 32;
+            if (resident2d_supported(o, tw, m)) {
+                ResidentArgs r{};
+                r.x = static_cast<const double*>(b.x);
+                r.p = static_cast<double*>(b.p);
+                r.st = r.mirror = b.st;
+                r.tol = 1e-300;
+                r.m_max = m;
+                for (int q = 0; q <= m; ++q) r.d[q] = 1e-3;
+                for (int q = 0; q < m; ++q) r.beta[q] = -0.5;
+                passes = std::min(passes, time_us([&] { return launch_resident2d(o, r, alpha, s); }) / m);
+            } else {
+                const int n = chain2d_length(o, 6) ? 6 : 4;
+                ChainArgs c{};
+                c.x = b.x;
+                c.out = b.out;
+                c.p = b.p;
+                c.partials = b.partials;
+                c.st = b.st;
+                c.alpha = alpha;
+                for (int q = 0; q < n; ++q) {
+                    c.beta[q] = -0.5;
+                    c.d[q] = 1e-3;
+                }
+                int np = 0;
+                const size_t room = partials_bytes(o);
+                passes = std::min(passes, time_us([&] {
+                           return launch_chain2d(o, tw, n, c, device_cus(), room, &np, s);
+                       }) / n);
+            }
+        }
+        if (err == hipSuccess) use_pairs = (passes < best_us) ? best_rows : 0;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -19,8 +19,9 @@ class Recorder:
 
 @pytest.mark.parametrize("shape,entry,pairs", [
     ((512, 300), {"pairs": True, "pair_rows": 32}, 32),
+    ((512, 300), {"pairs": False}, 1),                        # the other passes had not been timed
     ((512, 300), {"pairs": None}, 1),                         # a coefficient without pair sweeps
-    ((512, 300), {"pairs": False}, False),
+    ((512, 300), {"pairs": False, "passes_timed": True}, False),
     ((64, 64, 64), {"pairs": False}, False),
     ((64, 64, 64), {"pairs": True}, True),
     ((64, 64, 64), {}, 1),
