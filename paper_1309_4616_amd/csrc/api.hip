@@ -633,8 +633,9 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     }
     if (each) {
         // products 0 and 1 with tests (nearly constant vectors stop there),
-        // then chains of four
-        jd = jd >= 6 ? 2 + (jd - 2) / 4 * 4 : 0;
+        // then chains of four, and of two where those replace single products
+        if (jd < (C.pairs ? 6 : 4)) jd = 0;
+        else jd = C.pairs ? 2 + (jd - 2) / 4 * 4 : jd / 2 * 2;
         each = jd > 0;
     }
     TestPlan plan(C);
