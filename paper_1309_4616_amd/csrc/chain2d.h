@@ -9,11 +9,13 @@
 //
 // What bounds it: HBM beyond the last-level cache.  At 8192^2 FP64 a pass
 // of six products takes 464 us and moves 2.2 GB, a pair sweep 424 us, so
-// phi_1 of degree 25 takes 2.3 ms against 5.5 ms in pairs.  The arithmetic
-// (25 FP64 instructions per point and product, about 200 us for six) hides
-// behind the memory time at one or two waves per SIMD alike; a seventh level
-// would need a seventh slot in every queue.  On grids that fit the caches the
-// launches count: fewer of them, and fewer stop tests.
+// phi_1 of degree 25 takes 2.3 ms against 5.5 ms in pairs.  The arithmetic is
+// behind it, not far off: 25 FP64 instructions per point and product are 256
+// us for six at the device's 39e12 lane operations per second, about 280 with
+// what strips and tiles form twice, and the time is the same with one or two
+// waves per SIMD.  A seventh level would need a seventh slot in every queue.
+// On grids that fit the caches the launches count: fewer of them, and fewer
+// stop tests.
 //
 // Layout.  A wave owns a strip of 64 V columns and marches down `march` rows.
 // Level l is formed one row behind level l-1, so step s of the march brings

@@ -20,7 +20,11 @@
 // waves side by side cover a row, 8 / CX such groups cover the rows.  The
 // x neighbours come from the adjacent lanes by wave shifts, those beyond the
 // wave and the rows above and below from LDS (two copies, used in turn).
-// Points beyond the grid hold zero and have weight zero.
+// Points beyond the grid hold zero and have weight zero.  What fits: rows of
+// up to 64 points with 24 rows per wave (192 rows), up to 128 points with 16
+// (128 rows), and longer rows over CX waves with 12 rows per wave (129 to 256
+// points: 48 rows; up to 1024: 12); edge columns and one point per lane take
+// registers that more rows would need.
 #include <algorithm>
 #include <cmath>
 

@@ -419,7 +419,8 @@ size_t partials_bytes(const Op& op) {
         t.march = kMinMarch;
     }
     // also covers the pair sweep, whose grid never exceeds max(CU count, 8)
-    // workgroups of at most 8 partials each
+    // workgroups of at most 8 partials each; a chain sweep (16 partials each)
+    // cuts its grid to the room there is, here 256 workgroups at least
     const size_t grid = std::max<size_t>((size_t)make_geom(op, t).grid, 1024);
     return grid * 4 * sizeof(double);
 }
