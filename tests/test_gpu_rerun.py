@@ -99,3 +99,37 @@ def test_one_other_vector_is_no_evidence(E, name):
             E.phi_action(op, 1, tau, rough, tol=1e-10)
         _, s = E.phi_action(op, 1, tau, ones, tol=1e-10)
         assert s["degree_last"] == 2 and s["rerun_products"] == 0, seen
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("name", NAMES)
+def test_steps_run_again(E, name, dtype):
+    """Euler and Runge-Kutta steps whose loops stop early: the start vector is
+    formed again (alone, or inside the first pair sweep) and u is untouched
+    until the loop is accepted."""
+    new, n = make(E, name)
+    a, b = new().interval()
+    tol = 1e-10 if dtype == "f64" else 1e-6
+    rough = 0.5 + 0.1 * synth.uniform_vector(n, 1)
+    rerun = 0
+    for substeps in (1, 2):
+        tau = substeps * 13.0 / (b - a)
+        kw = dict(l_max=13.0 * (1 + 1e-9))
+        for step in (E.expeuler_step, E.exprk2_step):
+            for eps in (1e-2, 1e-6, 0.0):
+                u0 = 0.5 + eps * 0.1 * synth.uniform_vector(n, 2)
+                op = new()
+                for _ in range(6):
+                    step(op, tau, T(rough), tol=tol, dtype=dtype, params=E.LejaParams(**kw))
+                print(f"step again {name} {dtype} {step.__name__} {substeps} eps={eps}", flush=True)
+                u, z = T(u0), T(u0)
+                s = step(op, tau, u, tol=tol, dtype=dtype, params=E.LejaParams(**kw))
+                r = step(new(), tau, z, tol=tol, dtype=dtype, params=E.LejaParams(profile=True, fuse_start=1, **kw))
+                assert s["substeps"] == r["substeps"] == substeps
+                assert s["matvecs"] == r["matvecs"], (step.__name__, substeps, eps)
+                # u's own rounding in FP64; FP32 vectors enter through tau p
+                u, z = u.cpu().numpy(), z.cpu().numpy()
+                err = np.max(np.abs(u - z)) / np.max(np.abs(z))
+                assert err <= (1e-13 if dtype == "f64" else 10 * 2.0**-23), (step.__name__, substeps, eps, err)
+                rerun += s["rerun_products"]
+    assert rerun > 0
