@@ -631,11 +631,14 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         each = true;
         jd = estimate_degree(d, C.tol, C.m_max) / 2;
     }
+    const bool guessed = each && expected < 2;   // no loop seen
     if (each) {
         // products 0 and 1 with tests (nearly constant vectors stop there),
-        // then chains of four, and of two where those replace single products
+        // then chains, of four where the degree is a guess, and of two where
+        // those replace single products
         if (jd < (C.pairs ? 6 : 4)) jd = 0;
-        else jd = C.pairs ? 2 + (jd - 2) / 4 * 4 : jd / 2 * 2;
+        else if (!C.pairs) jd = jd / 2 * 2;
+        else if (guessed) jd = 2 + (jd - 2) / 4 * 4;
         each = jd > 0;
     }
     TestPlan plan(C);
@@ -891,7 +894,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
             // (const coefficient: 6, then 5 or 4 so that what is left is no
             // single product, and a pair for a remainder of 2; else 4 and 2)
             int n = 0;
-            const bool six = !each && chain2d_length(*C.op, 6);
+            const bool six = !guessed && chain2d_length(*C.op, 6);
             if (six && left >= 6 && left != 8 && left != 7 && left != 9) n = 6;
             else if (six && (left == 5 || left == 7 || left == 9)) n = 5;
             else if (left >= 4) n = 4;
