@@ -487,11 +487,16 @@ struct TestPlan {
 };
 
 // Bytes of partials a single product into vectors of storage code tw writes at
-// most (one point per lane).
+// most (stencils: with two points per lane or, where vectors are unaligned,
+// one, whose rows may be laid out differently).
 size_t single_partials(const Op& op, int tw) {
     Tiles t = product_tiles(op, tw, tw);
-    if (op.kind == 0) t.vec = 1;
-    return (size_t)make_geom(op, t).grid * 4 * sizeof(double);
+    int grid = make_geom(op, t).grid;
+    if (op.kind == 0) {
+        t.vec = 1;
+        grid = std::max(grid, make_geom(op, t).grid);
+    }
+    return (size_t)grid * 4 * sizeof(double);
 }
 
 // Estimate of the degree from the divided differences alone: where their

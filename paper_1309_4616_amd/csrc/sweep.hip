@@ -299,8 +299,9 @@ thread_local NewtonState* tl_mirror = nullptr;
 
 void set_state_mirror(NewtonState* mirror) { tl_mirror = mirror; }
 
-// Share of idle lanes (one in kFlatWaste) above which 3D rows go end to end.
+// Share of idle lanes (one in kFlatWaste) above which 3D rows may go end to end.
 constexpr int kFlatWaste = 16;
+constexpr int64_t kCus = 256;
 
 Geom make_geom(const Op& op, const Tiles& t) {
     Geom g{};
@@ -313,11 +314,24 @@ Geom make_geom(const Op& op, const Tiles& t) {
         g.tiles[1] = g.tiles[2] = 1;
     } else if (op.dim == 3) {
         // rows that leave many lanes of their last wave idle go end to end
+        // where there are more than two workgroups per CU, or end to end fewer
+        // per CU, or no more of them than XCDs.  Products of a stored
+        // coefficient, rows of their own against rows end to end: 450 x 256 x
+        // 256 (2048 workgroups, 1800) 315 and 287 us, 150 x 400 x 400 362 and
+        // 223; 150 x 130 x 111 (260, 156) 35 and 24, 24 x 200 x 200 30 and
+        // 22; 16 x 32 x 32 26 and 19.  But 96 x 256 x 256 (512, 384) 41 and
+        // 44, 200 x 200 x 100 (400, 316) 42 and 44, 40^3 19.9 and 20.7: the
+        // row of each lane has to be found.
         const int wx = 64 * t.vec, per_row = (op.n[0] + wx - 1) / wx;
-        g.flat = kFlatWaste * (per_row * wx - op.n[0]) > per_row * wx;
+        const int64_t plane = (int64_t)op.n[0] * op.n[1];
+        const int64_t planes = (op.n[2] + t.march - 1) / t.march;
+        const int64_t in_rows = (op.n[1] + t.waves - 1) / t.waves * (int64_t)per_row;
+        const int64_t flat = (plane + wx * t.waves - 1) / (wx * t.waves);
+        auto per_cu = [&](int64_t tiles) { return (tiles * planes + kCus - 1) / kCus; };
+        g.flat = kFlatWaste * (per_row * wx - op.n[0]) > per_row * wx &&
+                 (per_cu(in_rows) > 2 || per_cu(flat) < per_cu(in_rows) || in_rows * planes <= kXcd);
         if (g.flat) {
-            const int64_t plane = (int64_t)op.n[0] * op.n[1];
-            g.tiles[0] = (int)((plane + wx * t.waves - 1) / (wx * t.waves));
+            g.tiles[0] = (int)flat;
             g.tiles[1] = 1;
         } else {
             g.tiles[0] = per_row;
@@ -421,7 +435,13 @@ size_t partials_bytes(const Op& op) {
     // also covers the pair sweep, whose grid never exceeds max(CU count, 8)
     // workgroups of at most 8 partials each; a chain sweep (16 partials each)
     // cuts its grid to the room there is, here 256 workgroups at least
-    const size_t grid = std::max<size_t>((size_t)make_geom(op, t).grid, 1024);
+    size_t grid = std::max<size_t>((size_t)make_geom(op, t).grid, 1024);
+    if (op.kind == 0 && op.dim == 3) {
+        // (rows of their own take the most workgroups, whichever layout the
+        // smallest tiles have)
+        const size_t rows = (size_t)((op.n[0] + 63) / 64) * op.n[1] * ((op.n[2] + kMinMarch - 1) / kMinMarch);
+        grid = std::max(grid, (rows + kXcd - 1) / kXcd * kXcd);
+    }
     return grid * 4 * sizeof(double);
 }
 

@@ -55,12 +55,43 @@ int main() {
 """
 
 
-def test_one_chain_always_fits(tmp_path):
+SOURCE_3D = r"""
+#include <cstdio>
+#include "expi_internal.h"
+using namespace expi;
+int main() {
+    long bad = 0, seen = 0;
+    Op op;
+    op.kind = 0;
+    op.dim = 3;
+    op.coef = EXPI_COEF_CONST;
+    const int xs[] = {1, 2, 7, 16, 33, 63, 64, 65, 96, 120, 128, 129, 150, 200, 257, 512, 1000};
+    const int ys[] = {1, 2, 3, 8, 9, 40, 64, 65, 130, 250, 256, 700};
+    const int zs[] = {1, 3, 4, 5, 17, 32, 33, 111, 256};
+    for (int x : xs) for (int y : ys) for (int z : zs) {
+        op.n[0] = x; op.n[1] = y; op.n[2] = z;
+        op.size = (int64_t)x * y * z;
+        const size_t region = partials_bytes(op);
+        for (int vec : {1, 2}) for (int waves : {1, 2, 4, 8}) for (int march : {4, 8, 32, 120}) {
+            const Tiles t{vec, waves, march};
+            if (!tiles_valid(op, t)) continue;
+            ++seen;
+            if ((size_t)make_geom(op, t).grid * 32 > region && bad++ < 10)
+                std::printf("%d x %d x %d, tiles %d %d %d\n", x, y, z, vec, waves, march);
+        }
+    }
+    std::printf("%ld settings, %ld without room\n", seen, bad);
+    return bad != 0;
+}
+"""
+
+
+def run_program(tmp_path, source):
     if not os.path.exists(os.path.join(PKG, "libexpi.so")):
         from paper_1309_4616_amd import build
         build.build()
     src = tmp_path / "room.cpp"
-    src.write_text("#include <algorithm>\n" + SOURCE)
+    src.write_text("#include <algorithm>\n" + source)
     exe = str(tmp_path / "room")
     subprocess.run(["hipcc", "-O2", "-std=c++17", str(src), "-I", os.path.join(PKG, "csrc"), "-I",
                     os.path.join(ROOT, "include"), "-L", PKG, "-lexpi", "-Wl,-rpath," + PKG, "-o", exe], check=True,
@@ -68,3 +99,11 @@ def test_one_chain_always_fits(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     print(r.stdout)
     assert r.returncode == 0, r.stdout
+
+
+def test_one_chain_always_fits(tmp_path):
+    run_program(tmp_path, SOURCE)
+
+
+def test_products_fit_whichever_way_rows_are_laid_out(tmp_path):
+    run_program(tmp_path, SOURCE_3D)
