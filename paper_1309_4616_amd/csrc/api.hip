@@ -443,6 +443,25 @@ struct Ctx {
     int substep = 0;
 };
 
+// Bytes of partials a single product into vectors of storage code tw writes at
+// most (stencils: with two points per lane or, where vectors are unaligned,
+// one, whose rows may be laid out differently).
+size_t single_partials(const Op& op, int tw) {
+    Tiles t = product_tiles(op, tw, tw);
+    int grid = make_geom(op, t).grid;
+    if (op.kind == 0) {
+        t.vec = 1;
+        grid = std::max(grid, make_geom(op, t).grid);
+    }
+    return (size_t)grid * 4 * sizeof(double);
+}
+
+// The same of a launch of one Newton product or of a pair.
+size_t newton_partials(const Ctx& C, bool two) {
+    if (!two) return single_partials(*C.op, C.tw);
+    return C.op->dim == 2 ? pair2d_partials(*C.op, PAIR_NEWTON) : (size_t)pair_geom(*C.op, device_cus()).grid * 32;
+}
+
 // Partials of launches whose tests are deferred: each needs a place of its
 // own, taken from the workspace's partials region, then from `spare`.
 struct TestPlan {
@@ -457,6 +476,13 @@ struct TestPlan {
         t.tol = c.tol;
         t.roff = -1;
         untested = c.known != nullptr;
+    }
+    // Room for the sums of two launches at least: the tests of one by itself
+    // cost more than its finalize kernel (700^2 FP32, Euler step of two
+    // substeps, where nothing is spare: 455 us against 440).
+    bool holds_two() const {
+        const size_t bytes = align256(newton_partials(C, C.pairs));
+        return cap / bytes + C.spare_bytes / bytes >= 2;
     }
     // a place for `bytes` of partials (null: none left)
     double* place(size_t bytes, int n) {
@@ -485,19 +511,6 @@ struct TestPlan {
         used = used_spare = 0;
     }
 };
-
-// Bytes of partials a single product into vectors of storage code tw writes at
-// most (stencils: with two points per lane or, where vectors are unaligned,
-// one, whose rows may be laid out differently).
-size_t single_partials(const Op& op, int tw) {
-    Tiles t = product_tiles(op, tw, tw);
-    int grid = make_geom(op, t).grid;
-    if (op.kind == 0) {
-        t.vec = 1;
-        grid = std::max(grid, make_geom(op, t).grid);
-    }
-    return (size_t)grid * 4 * sizeof(double);
-}
 
 // Estimate of the degree from the divided differences alone: where their
 // two-term sum falls below the tolerance for terms of the start vector's
@@ -620,11 +633,12 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
     const bool defer_on = C.defer && !C.profile && !C.selector;
     const bool chain_first = defer_on && C.chains && !start_u && tin == C.tw && C.m_max >= 6;
     const bool known = C.known != nullptr;
+    TestPlan plan(C);
     int jd = 0;
     bool each = false;   // a test after every chain
     if (known) {
         jd = C.known->m;
-    } else if (defer_on && expected >= 2 && group >= 2 && (sure || C.chains)) {
+    } else if (defer_on && expected >= 2 && group >= 2 && (C.chains || (sure && plan.holds_two()))) {
         const int open = (start_u || !(first_pair || chain_first)) ? 1 : 2;
         const int end = std::min(group, C.m_max);
         jd = end - ((C.pairs && (C.chains || (end - open) % 2 == 0)) ? 2 : 1);
@@ -646,7 +660,6 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         else if (guessed) jd = 2 + (jd - 2) / 4 * 4;
         each = jd > 0;
     }
-    TestPlan plan(C);
     std::vector<int> tested;   // products that had run at each of the deferred tests
     int finalized = 0;
     int j = 0;
@@ -719,7 +732,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         if (known || (jd > 2 && !each)) {
             // the opening launch joins the deferred tests
             part0 = plan.place(!(start_u || first_pair) ? single_partials(*C.op, C.tw)
-                               : C.op->dim == 2         ? pair2d_partials(*C.op)
+                               : C.op->dim == 2         ? pair2d_partials(*C.op, PAIR_FIRST)
                                                         : (size_t)pair_geom(*C.op, device_cus()).grid * 64,
                                2);
             fin0 = part0 == nullptr;
@@ -920,10 +933,7 @@ int newton_loop(Ctx& C, const void* src, int tin, void* p, LoopOut* out, bool st
         }
         if (each) break;
         const bool two = C.pairs && left >= 2;
-        const size_t bytes = !two ? single_partials(*C.op, C.tw)
-                             : C.op->dim == 2 ? pair2d_partials(*C.op)
-                                              : (size_t)pair_geom(*C.op, device_cus()).grid * 32;
-        double* part = plan.place(bytes, two ? 2 : 1);
+        double* part = plan.place(newton_partials(C, two), two ? 2 : 1);
         if (!part) {
             if (plan.t.launches == 0) break;
             rc = flush();

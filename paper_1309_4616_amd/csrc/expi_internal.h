@@ -360,7 +360,7 @@ hipError_t launch_resident2d(const Op& op, ResidentArgs a, double alpha, hipStre
 // Bytes of partials a chain sweep of n products writes at most (no more than
 // `room`, which partials_bytes always is enough for).
 size_t chain2d_partials(const Op& op, int n, int cus, size_t room);
-size_t pair2d_partials(const Op& op);
+size_t pair2d_partials(const Op& op, int mode);
 // The stop tests of the launches in `t`, in order of their products: the
 // state as the finalize kernels of the launches would have left it.  A stop
 // that leaves later terms in p (other than the one a pair sweep leaves) is

@@ -298,10 +298,11 @@ bool pair2d_supported(const Op& op, int tw) {
 }
 
 // Bytes of partials a pair sweep writes at most (smallest tiles).
-size_t pair2d_partials(const Op& op) {
+size_t pair2d_partials(const Op& op, int mode) {
     const int64_t tiles = (int64_t)((op.n[0] + 63) / 64) * ((op.n[1] + 3) / 4);
     const int64_t wgs = (tiles + kP2Waves - 1) / kP2Waves;
-    return (size_t)std::min<int64_t>(kP2MaxGrid, (wgs + kXcd - 1) / kXcd * kXcd) * 8 * sizeof(double);
+    return (size_t)std::min<int64_t>(kP2MaxGrid, (wgs + kXcd - 1) / kXcd * kXcd) * (mode == PAIR_FIRST ? 8 : 4) *
+           sizeof(double);
 }
 
 // rows: rows per tile (pair2d_rows_valid), or 0 for 16, fewer where the
