@@ -8,7 +8,7 @@
 // written once: 32 B per point (FP64) for T products.
 //
 // What bounds it: HBM beyond the last-level cache.  At 8192^2 FP64 a pass
-// of six products takes 464 us and moves 2.2 GB, a pair sweep 424 us, so
+// of six products takes 464 to 470 us and moves 2.2 GB, a pair sweep 424, so
 // phi_1 of degree 25 takes 2.3 ms against 5.5 ms in pairs.  The arithmetic is
 // behind it, not far off: 25 FP64 instructions per point and product are 256
 // us for six at the device's 39e12 lane operations per second, about 280 with

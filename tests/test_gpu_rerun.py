@@ -87,13 +87,14 @@ def test_every_early_stop(E, name, dtype):
 
 @pytest.mark.parametrize("name", NAMES)
 def test_one_other_vector_is_no_evidence(E, name):
-    """A step length seen once, or thrice, with a rough vector: a constant one
-    then stops at degree 2 without a product run for nothing."""
+    """A step length seen once, or thrice where nothing runs in chains, with a
+    rough vector: a constant one then stops at degree 2 without a product run
+    for nothing."""
     new, n = make(E, name)
     op = new()
     a, b = op.interval()
     rough, ones = T(synth.uniform_vector(n, 1)), T(np.ones(n))
-    for q, seen in ((0.9, 0), (1.0, 1), (1.1, 3)):
+    for q, seen in ((0.9, 0), (1.0, 1), (1.1, 1 if name.endswith("2d") else 3)):
         tau = q * 13.0 / (b - a)
         for _ in range(seen):
             E.phi_action(op, 1, tau, rough, tol=1e-10)
