@@ -315,21 +315,27 @@ Geom make_geom(const Op& op, const Tiles& t) {
     } else if (op.dim == 3) {
         // rows that leave many lanes of their last wave idle go end to end
         // where there are more than two workgroups per CU, or end to end fewer
-        // per CU, or no more of them than XCDs.  Products of a stored
+        // per CU, or no more of them than XCDs, and rows of several waves with
+        // more than a quarter of the lanes idle also where there is no more
+        // than one per CU.  Products of a stored
         // coefficient, rows of their own against rows end to end: 450 x 256 x
         // 256 (2048 workgroups, 1800) 315 and 287 us, 150 x 400 x 400 362 and
         // 223; 150 x 130 x 111 (260, 156) 35 and 24, 24 x 200 x 200 30 and
-        // 22; 16 x 32 x 32 26 and 19.  But 96 x 256 x 256 (512, 384) 41 and
-        // 44, 200 x 200 x 100 (400, 316) 42 and 44, 40^3 19.9 and 20.7: the
-        // row of each lane has to be found.
+        // 22; 16 x 32 x 32 26 and 19; 71 x 36 x 32 20.4 and 18.7, 260 x 30 x
+        // 30 24.5 and 20.5.  But 96 x 256 x 256 (512, 384) 41 and 44, 200 x
+        // 200 x 100 (400, 316) 42 and 44, 40^3 19.9 and 20.7, 72 x 36 x 32
+        // 20.0 and 20.9, 200 x 64 x 40 21.4 and 21.9: the row of each lane has
+        // to be found.
         const int wx = 64 * t.vec, per_row = (op.n[0] + wx - 1) / wx;
         const int64_t plane = (int64_t)op.n[0] * op.n[1];
         const int64_t planes = (op.n[2] + t.march - 1) / t.march;
         const int64_t in_rows = (op.n[1] + t.waves - 1) / t.waves * (int64_t)per_row;
         const int64_t flat = (plane + wx * t.waves - 1) / (wx * t.waves);
         auto per_cu = [&](int64_t tiles) { return (tiles * planes + kCus - 1) / kCus; };
-        g.flat = kFlatWaste * (per_row * wx - op.n[0]) > per_row * wx &&
-                 (per_cu(in_rows) > 2 || per_cu(flat) < per_cu(in_rows) || in_rows * planes <= kXcd);
+        const int idle = per_row * wx - op.n[0];
+        g.flat = kFlatWaste * idle > per_row * wx &&
+                 (per_cu(in_rows) > 2 || per_cu(flat) < per_cu(in_rows) || in_rows * planes <= kXcd ||
+                  (per_row > 1 && 4 * idle > per_row * wx && per_cu(in_rows) == 1));
         if (g.flat) {
             g.tiles[0] = (int)flat;
             g.tiles[1] = 1;

@@ -1,9 +1,11 @@
 """3D products on both sides of the rule that lays rows end to end: where that
 takes fewer workgroups per CU (150 x 130 x 100: 260 in rows of their own, 156
-end to end; 16 x 250 x 250: 504 and 64), where there are many (200 x 200 x 140:
+end to end; 16 x 250 x 250: 504 and 64), where rows of several waves leave many
+lanes idle (71 x 36 x 32), where there are many workgroups (200 x 200 x 140:
 500 and 395, with one point per lane 1000 and 785) and where rows stay apart
-(48^3; 200 x 64 x 40), with two points per lane and with one, aligned and not.  The bound of
-tests/test_gpu_flat_rows.py: 16 roundings of the largest term.
+(48^3; 72 x 36 x 32; 200 x 64 x 40), with two points per lane and with one,
+aligned and not.  The bound of tests/test_gpu_flat_rows.py: 16 roundings of the
+largest term.
 """
 import numpy as np
 import pytest
@@ -13,7 +15,7 @@ from oracle import operators as O
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape", [(150, 130, 100), (16, 250, 250), (48, 48, 48), (200, 64, 40),
+@pytest.mark.parametrize("shape", [(150, 130, 100), (16, 250, 250), (48, 48, 48), (200, 64, 40), (71, 36, 32), (72, 36, 32),
                                    (200, 200, 140)])
 @pytest.mark.parametrize("kind", ["const", "field"])
 def test_both_layouts(shape, kind):
